@@ -185,3 +185,20 @@ def test_prefill_rejects_fp32():
     with pytest.raises(B.PrhsError) as e:
         B.prhs_prefill_attn(kv, q, 0.125, out)
     assert e.value.status == B.PRHS_E_UNSUPPORTED
+
+
+@pytest.mark.parametrize("batch,hq,T,d,paged", [
+    (1, 2, 127, 128, False),    # four key sides: the edges of 64-query blocks and 128-key tiles
+    (1, 2, 129, 64, True),
+    (3, 24, 257, 128, True),    # two key sides: 128-query blocks (on 256 CUs)
+    (3, 24, 384, 64, False),
+    (3, 60, 255, 128, False),   # one key side: 256-query blocks, units not a multiple of the XCDs
+    (5, 24, 321, 128, True),    # units a multiple of the XCDs, not of a whole group of them
+])
+def test_prefill_key_sides_and_block_order(batch, hq, T, d, paged):
+    # outputs as for every other prefill test: bf16 hi + lo probabilities
+    lens = tuple(max(1, T - 61 * i) for i in range(batch))
+    rows = sorted({0, 31, 32, 63, 64, 127, 128, 191, 192, 255, 256, T // 2, T - 62, T - 1})
+    run_prefill(batch, hq, min(hq, 4), d, lens, T, psaw=(2, 0.6, 1.0), layer=3, n_layers=4, sink=5,
+                seed=41 + T, rows=[r for r in rows if 0 <= r < T], heads=[0, hq // 2, hq - 1],
+                paged=paged)
