@@ -34,10 +34,11 @@
 // order; the dimension order inside a row is permuted identically on K and
 // Q.  V needs no transpose: a lane's 8 rows x 8 dims block feeds the second
 // product directly.  K and V bytes are read once, with the streaming policy.
-// fp32 inputs take a vector-ALU path (16 lanes per row, one query head per
-// workgroup).
+// fp32 inputs take a vector-ALU path (d/4 lanes per row, all query heads of a
+// unit in one workgroup).
 #include <stdlib.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "prhs_internal.h"
@@ -51,9 +52,20 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 constexpr float kLn2 = 0.69314718055994530942f;
 constexpr int kRowsPerThread = 8;   // staged list entries per thread
 constexpr int kMaxSplits = 4096;
+constexpr int kMaxWaves = 8;        // waves of an attention workgroup
 // Sparse sets of at most this many rows per unit are not split: a launch of
-// one workgroup per unit beats a split launch plus its merge launch.
+// one workgroup per unit beats a split launch plus its merge launch (fp32
+// rows are twice as long: 32 units of 500 rows 20.7 us unsplit, 13.4 split; 4
+// units of 150 rows 5.6 and 7.9).
 constexpr int kNoSplitRows = 512;
+constexpr int kNoSplitRowsF32 = 256;
+// fp32 splits: at least kMinRowsF32 rows, and no more than kMergeSplitsF32 of
+// them per unit once the launch has 256 workgroups, since the merge reads
+// every split's output of every head (dense, 8 units of 4 heads at d 128:
+// 2000 rows in 125 splits 18.3 us, in 32 13.6; 8000 rows in 125 26.5, in 32
+// 19.8).
+constexpr int kMinRowsF32 = 64;
+constexpr long long kMergeSplitsF32 = 32;
 
 struct AttnArgs {
   KvView kv;
@@ -576,104 +588,225 @@ __global__ __launch_bounds__(512) void attn_split_bf16(AttnArgs a) {
   }
 }
 
-template <int D, bool DENSE, bool PAGED>
-__global__ __launch_bounds__(256) void attn_split_f32(AttnArgs a) {
-  constexpr int DPL = D / 16;
-  __shared__ float sm_m[4], sm_l[4];
-  __shared__ float sm_o[4][D];
-  __shared__ int32_t s_row[256 * kRowsPerThread];
-  const int split = blockIdx.x, bh = blockIdx.y;
-  const int hkv = a.kv.hkv, hq = a.kv.hq, G = hq / hkv;
-  const int b = bh / hq, h = bh % hq, g = h / G, u = b * hkv + g;
+// Loads of K and of V per wave step (registers bound it).
+constexpr int f32_loads(int GP) { return 4; }
+
+// fp32 inputs on the vector ALU: one workgroup per (unit, split) for up to
+// GP = 1, 2, 4 or 8 of the unit's query heads together, so K and V are read
+// once (twice for 9 to 16 heads, whose state would not fit the registers)
+// and not once per query head.  A row is D / 4 lanes of
+// 16 bytes, so a wave load takes RPI whole rows; each step takes U loads of K
+// and of V, the next step's in flight while one is multiplied.  A lane keeps
+// 4 dims of every head's query and output; the dot products are summed over
+// a row's lanes by DPP moves.  What bounds it: HBM on many rows, the chain of
+// length, row id and row loads (about 7 us a launch) on few.  Against one
+// workgroup per query head, which read every row once per head with one load
+// in flight (at d 128, sets of 500 rows in 32 units of 4 heads: 27.3 -> 13.4
+// us; dense, 128 units of 4 heads over 4000 rows, 524 MB: 289 -> 99 us,
+// 5.3 TB/s).
+template <int U>
+struct F32Rows {
+  float4 k[U], v[U];
+  uint32_t ok;
+};
+
+template <int D, int U>
+__device__ __forceinline__ void load_rows_f32(F32Rows<U>& T, const int32_t* s_row, int t, int n,
+                                              const float* kb, const float* vb, int lane) {
+  constexpr int LPR = D / 4, RPI = 64 / LPR;
+  const int c = lane % LPR, sub = lane / LPR;
+  int row[U];
+#pragma unroll
+  for (int j = 0; j < U; ++j) {
+    const int r = t + j * RPI + sub;
+    const int x = s_row[min(r, n - 1)];
+    row[j] = r < n ? x : -1;
+  }
+  T.ok = 0u;
+#pragma unroll
+  for (int j = 0; j < U; ++j) {
+    const int64_t off = (int64_t)(row[j] < 0 ? 0 : row[j]) * D + c * 4;
+    T.k[j] = stream_load_f32x4(kb + off);
+    T.v[j] = stream_load_f32x4(vb + off);
+    if (row[j] >= 0) T.ok |= 1u << j;
+  }
+}
+
+template <int D, int GP, int U>
+__device__ __forceinline__ void consume_rows_f32(F32Rows<U>& T, const float4 (&q)[GP], float scale_log2,
+                                                 float (&m)[GP], float (&l)[GP], float4 (&o)[GP]) {
+  constexpr int LPR = D / 4;
+  // a row outside the set or the cache read a stand-in row
+#pragma unroll
+  for (int j = 0; j < U; ++j)
+    if (!((T.ok >> j) & 1u)) T.v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+  float x[U][GP], mn[GP];
+  bool rise = false;
+#pragma unroll
+  for (int h = 0; h < GP; ++h) {
+    float mt = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      float s = q[h].x * T.k[j].x;
+      s = fmaf(q[h].y, T.k[j].y, s);
+      s = fmaf(q[h].z, T.k[j].z, s);
+      s = fmaf(q[h].w, T.k[j].w, s);
+      s = group_sum<LPR>(s);
+      x[j][h] = ((T.ok >> j) & 1u) ? s * scale_log2 : -INFINITY;
+      mt = fmaxf(mt, x[j][h]);
+    }
+    // over the wave's row groups: they share one softmax state
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(mt), __float_as_uint(mt), false, false);
+    mt = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    if (LPR == 16) {
+      const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(mt), __float_as_uint(mt), false, false);
+      mt = fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    }
+    mn[h] = fmaxf(m[h], mt);
+    rise = rise || mn[h] > m[h] + 8.f;
+  }
+  // lazy rescaling, as in the bf16 kernel: probabilities stay below 2^8
+  if (__builtin_amdgcn_ballot_w64(rise)) {
+#pragma unroll
+    for (int h = 0; h < GP; ++h) {
+      const float alpha = mn[h] == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m[h] - mn[h]);
+      m[h] = mn[h];
+      l[h] *= alpha;
+      o[h].x *= alpha; o[h].y *= alpha; o[h].z *= alpha; o[h].w *= alpha;
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < GP; ++h) {
+    const float mref = m[h] == -INFINITY ? 0.f : m[h];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const float p = __builtin_amdgcn_exp2f(x[j][h] - mref);
+      l[h] += p;
+      o[h].x = fmaf(p, T.v[j].x, o[h].x);
+      o[h].y = fmaf(p, T.v[j].y, o[h].y);
+      o[h].z = fmaf(p, T.v[j].z, o[h].z);
+      o[h].w = fmaf(p, T.v[j].w, o[h].w);
+    }
+  }
+}
+
+// Sum over a wave's row groups (lanes of equal dims), in every lane.
+template <int LPR>
+__device__ __forceinline__ float over_row_groups(float v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  if (LPR == 16) {
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  }
+  return v;
+}
+
+template <int D, int GP, bool DENSE>
+__global__ __launch_bounds__(64 * kMaxWaves) void attn_split_f32(AttnArgs a) {
+  constexpr int LPR = D / 4, RPI = 64 / LPR;
+  constexpr int U = f32_loads(GP), ROWS = U * RPI;
+  // dynamic LDS: [nwaves][GP][D] wave outputs, then the staged row ids
+  extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+  __shared__ float sm_m[kMaxWaves][16];
+  __shared__ float sm_l[kMaxWaves][16];
+  const int hkv = a.kv.hkv, hq = a.kv.hq;
+  const int parts = (hq / hkv + GP - 1) / GP;  // workgroups that share a unit's heads
+  const int split = blockIdx.x, u = blockIdx.y / parts;
+  const int h0 = (blockIdx.y % parts) * GP, G = min(hq / hkv - h0, GP);  // this one's heads
+  const int b = u / hkv, g = u % hkv;
+  const size_t qh0 = (size_t)b * hq + g * (hq / hkv) + h0;
+  const int nwaves = blockDim.x >> 6;
+  float* s_o = (float*)dyn;
+  int32_t* s_row = (int32_t*)(s_o + (size_t)nwaves * GP * D);
   const int start = split * a.chunk;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int c = lane % LPR, sub = lane / LPR;
   int32_t raw[kRowsPerThread];
   prefetch_entries<DENSE>(a, u, start, raw);
+  const float* qp = (const float*)a.q + qh0 * D + c * 4;
+  float4 q[GP];
+#pragma unroll
+  for (int h = 0; h < GP; ++h) q[h] = h < G ? load_f32x4(qp + h * D) : make_float4(0.f, 0.f, 0.f, 0.f);
   const int nb = kv_seq_len(a.kv, b);
   if (!DENSE && unit_excluded(a, u)) return;
   const UnitSpan sp = unit_span<DENSE>(a, u, b, nb);
   const int L = sp.L;
   if (L == 0 && split == 0) {  // empty set: y = 0, lse = -inf
-    for (int dim = threadIdx.x; dim < D; dim += blockDim.x)
-      write_final(a, bh, D, dim, -INFINITY, 0.f, 0.f);
+    for (int e = threadIdx.x; e < G * D; e += blockDim.x)
+      write_final(a, qh0 + e / D, D, e % D, -INFINITY, 0.f, 0.f);
     return;
   }
   if (start >= L) return;
   const int n = min(L, start + a.chunk) - start;
-  const int nwaves = blockDim.x >> 6;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int rg = lane >> 4, c = lane & 15;
-  const float* qp = (const float*)a.q + (size_t)bh * D + c * DPL;
-  float qv[DPL];
-#pragma unroll
-  for (int i = 0; i < DPL; ++i) qv[i] = qp[i];
-  stage_rows<DENSE, PAGED>(a, raw, start, n, sp, nb, b, g, s_row);
+  if (a.kv.paged) stage_rows<DENSE, true>(a, raw, start, n, sp, nb, b, g, s_row);
+  else stage_rows<DENSE, false>(a, raw, start, n, sp, nb, b, g, s_row);
   const float* kb = (const float*)a.kv.k;
   const float* vb = (const float*)a.kv.v;
-  float m_run = -INFINITY, l_run = 0.f, o[DPL];
+  float m[GP], l[GP];
+  float4 o[GP];
 #pragma unroll
-  for (int i = 0; i < DPL; ++i) o[i] = 0.f;
-  for (int t = wave * 4; t < n; t += 4 * nwaves) {
-    const int r = t + rg;
-    const int row = r < n ? s_row[r] : -1;
-    const float* kp = kb + (int64_t)(row < 0 ? 0 : row) * D + c * DPL;
-    const float* vp = vb + (int64_t)(row < 0 ? 0 : row) * D + c * DPL;
-    float kx[DPL], vx[DPL];
-#pragma unroll
-    for (int i = 0; i < DPL; ++i) {
-      kx[i] = kp[i];
-      vx[i] = vp[i];
+  for (int h = 0; h < GP; ++h) {
+    m[h] = -INFINITY;
+    l[h] = 0.f;
+    o[h] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  // this wave's steps: wave, wave + nwaves, ...
+  const int nsteps = (n + ROWS - 1) / ROWS;
+  const int iters = wave < nsteps ? (nsteps - wave + nwaves - 1) / nwaves : 0;
+  if (iters > 0) {
+    F32Rows<U> A, B;
+    const int stride = ROWS * nwaves;
+    int t = wave * ROWS;
+    load_rows_f32<D, U>(A, s_row, t, n, kb, vb, lane);
+    int i = 0;
+    for (; i + 2 < iters; i += 2) {
+      load_rows_f32<D, U>(B, s_row, t + stride, n, kb, vb, lane);
+      consume_rows_f32<D, GP, U>(A, q, a.scale_log2, m, l, o);
+      load_rows_f32<D, U>(A, s_row, t + 2 * stride, n, kb, vb, lane);
+      consume_rows_f32<D, GP, U>(B, q, a.scale_log2, m, l, o);
+      t += 2 * stride;
     }
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < DPL; ++i) s = fmaf(qv[i], kx[i], s);
-#pragma unroll
-    for (int w = 1; w < 16; w <<= 1) s += __shfl_xor(s, w, 16);
-    const float x = row >= 0 ? s * a.scale_log2 : -INFINITY;
-    float mt = fmaxf(x, __shfl_xor(x, 16));
-    mt = fmaxf(mt, __shfl_xor(mt, 32));
-    const float m_new = fmaxf(m_run, mt);
-    float alpha = 1.f, p = 0.f;
-    if (m_new != -INFINITY) {
-      alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-      p = row >= 0 ? __builtin_amdgcn_exp2f(x - m_new) : 0.f;
+    if (i + 1 < iters) {
+      load_rows_f32<D, U>(B, s_row, t + stride, n, kb, vb, lane);
+      consume_rows_f32<D, GP, U>(A, q, a.scale_log2, m, l, o);
+      consume_rows_f32<D, GP, U>(B, q, a.scale_log2, m, l, o);
+    } else {
+      consume_rows_f32<D, GP, U>(A, q, a.scale_log2, m, l, o);
     }
-    l_run = l_run * alpha + p;
-#pragma unroll
-    for (int i = 0; i < DPL; ++i) o[i] = o[i] * alpha + (row >= 0 ? p * vx[i] : 0.f);
-    m_run = m_new;
   }
 #pragma unroll
-  for (int i = 0; i < DPL; ++i) {
-    o[i] += __shfl_xor(o[i], 16);
-    o[i] += __shfl_xor(o[i], 32);
-  }
-  l_run += __shfl_xor(l_run, 16);
-  l_run += __shfl_xor(l_run, 32);
-  if (lane < 16) {
-#pragma unroll
-    for (int i = 0; i < DPL; ++i) sm_o[wave][c * DPL + i] = o[i];
-  }
-  if (lane == 0) {
-    sm_m[wave] = m_run;
-    sm_l[wave] = l_run;
+  for (int h = 0; h < GP; ++h) {
+    l[h] = over_row_groups<LPR>(l[h]);
+    o[h].x = over_row_groups<LPR>(o[h].x);
+    o[h].y = over_row_groups<LPR>(o[h].y);
+    o[h].z = over_row_groups<LPR>(o[h].z);
+    o[h].w = over_row_groups<LPR>(o[h].w);
+    if (sub == 0) *(float4*)(s_o + ((size_t)wave * GP + h) * D + c * 4) = o[h];
+    if (lane == 0) {
+      sm_m[wave][h] = m[h];
+      sm_l[wave][h] = l[h];
+    }
   }
   __syncthreads();
   const int nsp = (L + a.chunk - 1) / a.chunk;
-  for (int dim = threadIdx.x; dim < D; dim += blockDim.x) {
+  for (int e = threadIdx.x; e < G * D; e += blockDim.x) {
+    const int h = e / D, dim = e - h * D;
     float M = -INFINITY;
-    for (int w = 0; w < nwaves; ++w) M = fmaxf(M, sm_m[w]);
+    for (int w = 0; w < nwaves; ++w) M = fmaxf(M, sm_m[w][h]);
     float num = 0.f, den = 0.f;
     if (M != -INFINITY) {
       for (int w = 0; w < nwaves; ++w) {
-        const float f = __builtin_amdgcn_exp2f(sm_m[w] - M);
-        num += f * sm_o[w][dim];
-        den += f * sm_l[w];
+        const float f = __builtin_amdgcn_exp2f(sm_m[w][h] - M);
+        num += f * s_o[((size_t)w * GP + h) * D + dim];
+        den += f * sm_l[w][h];
       }
     }
+    const size_t bh = qh0 + h;
     if (nsp == 1) {
       write_final(a, bh, D, dim, M, num, den);
     } else {
-      const size_t pidx = (size_t)bh * a.nsplit + split;
+      const size_t pidx = bh * a.nsplit + split;
       a.part_o[pidx * D + dim] = num;
       if (dim == 0) {
         a.part_ml[pidx * 2] = M;
@@ -802,6 +935,20 @@ int wave_limit() {
   return v;
 }
 
+template <int D, int GP, bool DENSE>
+hipError_t launch_f32(const AttnArgs& a, int units, int waves, hipStream_t stream) {
+  const size_t dyn = (size_t)waves * GP * D * sizeof(float) +
+                     (size_t)64 * waves * kRowsPerThread * sizeof(int32_t);
+  if (dyn > 65536) {
+    const hipError_t e = hipFuncSetAttribute((const void*)attn_split_f32<D, GP, DENSE>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((attn_split_f32<D, GP, DENSE>), dim3(a.nsplit, units * ((a.kv.hq / a.kv.hkv + GP - 1) / GP)),
+                     dim3(64 * waves), dyn, stream, a);
+  return hipSuccess;
+}
+
 template <int D, bool DENSE, bool PAGED>
 hipError_t launch_typed(const AttnArgs& a, int dtype, int units, int waves, hipStream_t stream) {
   if (dtype == 1) {
@@ -816,8 +963,18 @@ hipError_t launch_typed(const AttnArgs& a, int dtype, int units, int waves, hipS
     hipLaunchKernelGGL((attn_split_bf16<D, DENSE, PAGED>), dim3(a.nsplit, units), dim3(64 * waves),
                        dyn, stream, a);
   } else {
-    hipLaunchKernelGGL((attn_split_f32<D, DENSE, PAGED>), dim3(a.nsplit, units), dim3(256), 0,
-                       stream, a);
+    // heads per workgroup: all (up to 8), or fewer while the launch would
+    // leave CUs without a workgroup, where the heads' serial work costs more
+    // than reading the rows again from the caches (8 units of 8
+    // heads over 60 rows at d 64: 8 heads 8.0 us, 4 6.3, 2 5.8, 1 6.1)
+    const int G = a.kv.hq / a.kv.hkv;
+    int gp = G == 1 ? 1 : (G == 2 ? 2 : (G <= 4 ? 4 : 8));
+    while (gp > 2 && (long long)units * a.nsplit * ((G + gp - 1) / gp) < device_cus()) gp >>= 1;
+    const hipError_t e = gp == 1   ? launch_f32<D, 1, DENSE>(a, units, waves, stream)
+                         : gp == 2 ? launch_f32<D, 2, DENSE>(a, units, waves, stream)
+                         : gp == 4 ? launch_f32<D, 4, DENSE>(a, units, waves, stream)
+                                   : launch_f32<D, 8, DENSE>(a, units, waves, stream);
+    if (e != hipSuccess) return e;
   }
   if (a.nsplit > 1)
     hipLaunchKernelGGL((attn_merge<D, DENSE>), dim3(a.kv.batch * a.kv.hq), dim3(256), 0, stream,
@@ -839,8 +996,14 @@ AttnLayout attn_layout(int batch, int hq, int d, int nsplit) {
   return L;
 }
 
-int waves_for(int dtype, int chunk) {
-  if (dtype != 1) return 4;
+int waves_for(int dtype, long long groups, int chunk) {
+  // fp32: a wave per 16 rows where the workgroups are fewer than two per CU
+  // (all rows load at once), else per 32 (less to combine: 1248 units of 60
+  // rows 14.1 -> 12.9 us, dense 32 units of 4001 rows 38.8 -> 30.7)
+  if (dtype != 1) {
+    const int rows = groups < 2LL * device_cus() ? 16 : 32;
+    return std::min(kMaxWaves, (chunk + rows - 1) / rows);
+  }
   int w = chunk / 32;
   const int lim = wave_limit();
   return w < 1 ? 1 : (w > lim ? lim : w);
@@ -855,15 +1018,20 @@ int waves_for(int dtype, int chunk) {
 void attn_split_geometry(int dtype, bool dense, int batch, int hq, int hkv, int rows_cap,
                          int* chunk, int* nsplit) {
   const int gran = dtype == 1 ? 32 : 16;
-  const long long units = dtype == 1 ? (long long)batch * hkv : (long long)batch * hq;
+  const long long units = (long long)batch * hkv;
   const long long rows = rows_cap > 0 ? rows_cap : 1;
   const long long tg = target_groups(dense);
   long long c = (rows * (units > 0 ? units : 1) + tg - 1) / tg;
   const long long cmin = (rows + kMaxSplits - 1) / kMaxSplits;
+  if (dtype != 1) {
+    const long long fill = (rows * (units > 0 ? units : 1) + 255) / 256;
+    c = std::max(c, std::min((rows + kMergeSplitsF32 - 1) / kMergeSplitsF32, fill));
+    c = std::max<long long>(c, kMinRowsF32);
+  }
   if (c < cmin) c = cmin;
   const long long threads = dtype == 1 ? 64LL * wave_limit() : 256;
   const long long cmax = threads * kRowsPerThread;
-  if (!dense && rows <= kNoSplitRows && rows <= cmax) c = rows;
+  if (!dense && rows <= (dtype == 1 ? kNoSplitRows : kNoSplitRowsF32) && rows <= cmax) c = rows;
   if (c > cmax) c = cmax;
   if (c < gran) c = gran;
   const long long ns = (rows + c - 1) / c;
@@ -932,8 +1100,8 @@ hipError_t launch_attention(const AttnLaunch& s, bool dense, hipStream_t stream)
   a.part_ml = (float*)(ws + L.part_ml);
   a.out = s.out;
   a.lse = s.lse;
-  const int waves = waves_for(s.dtype, a.chunk);
-  const int units = s.dtype == 1 ? s.kv.batch * s.kv.hkv : s.kv.batch * s.kv.hq;
+  const int units = s.kv.batch * s.kv.hkv;
+  const int waves = waves_for(s.dtype, (long long)units * a.nsplit, a.chunk);
   const bool paged = s.kv.paged != 0;
 #define PRHS_ATTN_DISPATCH(DV)                                                          \
   if (dense) {                                                                          \

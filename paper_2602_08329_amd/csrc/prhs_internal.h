@@ -29,6 +29,17 @@ __device__ __forceinline__ u32x2_t stream_load8(const void* p) {
   return __builtin_nontemporal_load((const u32x2_t*)p);
 }
 
+// Four floats of an fp32 tensor, whose rows are aligned to 4 bytes only.
+typedef float f32x4_a4_t __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load_f32x4(const float* p) {
+  const f32x4_a4_t v = *(const f32x4_a4_t*)p;
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+__device__ __forceinline__ float4 stream_load_f32x4(const float* p) {
+  const f32x4_a4_t v = __builtin_nontemporal_load((const f32x4_a4_t*)p);
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+
 // Device view of one layer's KV cache.
 struct KvView {
   const void* k;
@@ -178,6 +189,25 @@ __device__ __forceinline__ T block_exclusive_scan(T v, T* scratch, T* total) {
   // caller reaches a barrier before it writes scratch again)
   if (REUSE_BARRIER) lds_barrier();
   return before + x - v;
+}
+
+// Sum over aligned groups of LANES = 16 or 32 lanes, in every lane of the
+// group: rotations by 8, 4, 2 and 1 inside each row of 16 lanes (DPP
+// row_ror), then the neighbouring row by the cross-row swap, which leaves a
+// lane holding its own value and its partner's.
+template <int CTRL>
+__device__ __forceinline__ float add_rotated(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+template <int LANES>
+__device__ __forceinline__ float group_sum(float v) {
+  static_assert(LANES == 16 || LANES == 32, "lane groups of one or two rows");
+  v = add_rotated<0x121>(add_rotated<0x122>(add_rotated<0x124>(add_rotated<0x128>(v))));
+  if (LANES == 32) {
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  }
+  return v;
 }
 
 // ---------------------------------------------------------------------------

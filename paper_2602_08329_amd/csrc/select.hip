@@ -46,6 +46,7 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kScoreBlock = 256;
 constexpr int kScoreChunk = 1024;   // keys per score workgroup
+constexpr int kScoreChunkF32 = 256; // the same of score_f32 without histograms
 constexpr int kScoreSub = 2;        // 16-key sub-tiles per wave step of score_bf16
 constexpr int kFilterBlock = 256;
 constexpr int kFilterPerThread = 16;
@@ -371,51 +372,84 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(4))
   }
 }
 
-// fp32 scoring on the vector ALU: one key per thread, the group's query heads
-// staged in LDS, sequential fp32 fused multiply-adds over d.
+// fp32 scoring on the vector ALU: a key is D / 4 lanes of 16 bytes, so a wave
+// load takes whole keys, U loads in flight, which stay in registers over the
+// group's query heads; the dot products are summed over a key's lanes by DPP
+// moves.  Workgroups are kScoreChunk keys with histograms, whose flush costs
+// atomics, and kScoreChunkF32 without, so that short rows still spread over
+// the CUs.  What bounds it: HBM.  32 rows of 3000 keys, 4 heads, d 128
+// (49 MB): 70 -> 16 us against a thread per key, whose loads were 64 pieces of
+// 16 bytes.
 template <int D, bool HIST>
 __global__ __launch_bounds__(kScoreBlock) void score_f32(SelArgs a) {
-  __shared__ __attribute__((aligned(8))) uint32_t hist[kHistBins];
-  __shared__ float qs[16 * D];
+  constexpr int LPK = D / 4, KPI = 64 / LPK;  // lanes per key, keys per load
+  constexpr int U = 8;                        // loads per step
+  constexpr int STEP = U * KPI;               // keys per wave step
+  constexpr int CHUNK = HIST ? kScoreChunk : kScoreChunkF32;
+  constexpr int WKEYS = CHUNK / (kScoreBlock / 64);  // keys per wave
+  static_assert(WKEYS % 64 == 0 && 64 % STEP == 0, "whole 64-key runs of whole steps");
+  __shared__ __attribute__((aligned(8))) uint32_t hist[HIST ? kHistBins : 2];
+  __shared__ __attribute__((aligned(16))) float qs[16 * D];
   const int row = blockIdx.y;
   if (row_skipped(a, row)) return;
   const int b = row / a.kv.hkv, g = row % a.kv.hkv;
   const RowGeom rg = row_geom(a, b);
-  const int base = blockIdx.x * kScoreChunk;
+  const int base = blockIdx.x * CHUNK;
   if (base >= rg.m || rg.kb <= 0) return;
-  const int end = min(rg.m, base + kScoreChunk);
+  const int end = min(rg.m, base + CHUNK);
   const int G = a.kv.hq / a.kv.hkv;
-  const float* q = (const float*)a.q;
-  for (int i = threadIdx.x; i < kHistBins; i += kScoreBlock) hist[i] = 0u;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int c = lane % LPK, sub = lane / LPK;
+  if (HIST)
+    for (int i = threadIdx.x; i < kHistBins; i += kScoreBlock) hist[i] = 0u;
   for (int i = threadIdx.x; i < G * D; i += kScoreBlock)
-    qs[i] = q[((size_t)b * a.kv.hq + g * G) * D + i];
+    qs[i] = ((const float*)a.q)[((size_t)b * a.kv.hq + g * G) * D + i];
   __syncthreads();
   const float* kb = (const float*)a.kv.k;
   uint32_t* keys = a.keys + (size_t)row * a.mcap;
-  for (int i = base + threadIdx.x; i < end; i += kScoreBlock) {
-    const int64_t off = kv_row_offset(a.kv, b, g, rg.sink_end + i);
-    float best = -INFINITY;
-    for (int h = 0; h < G; ++h) {
-      float acc = 0.f;
-      if (off >= 0) {
-        const float4* kp = (const float4*)(kb + off);
-        for (int j = 0; j < D / 4; ++j) {
-          const float4 x = kp[j];
-          const float* qh = qs + h * D + 4 * j;
-          acc = fmaf(qh[0], x.x, acc);
-          acc = fmaf(qh[1], x.y, acc);
-          acc = fmaf(qh[2], x.z, acc);
-          acc = fmaf(qh[3], x.w, acc);
+  for (int r0 = base + wave * WKEYS; r0 < min(end, base + (wave + 1) * WKEYS); r0 += 64) {
+    // row id of key r0 + lane (a key past the end or outside the cache: none)
+    const int64_t off = r0 + lane < end ? kv_row_offset(a.kv, b, g, rg.sink_end + r0 + lane) : -1;
+    const int rid = off < 0 ? -1 : (int)(off / D);
+    for (int t = 0; t < 64 && r0 + t < end; t += STEP) {
+      float4 k[U];
+      uint32_t ok = 0;
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int id = __shfl(rid, t + j * KPI + sub);
+        k[j] = stream_load_f32x4(kb + (int64_t)(id < 0 ? 0 : id) * D + c * 4);
+        ok |= (id >= 0 ? 1u : 0u) << j;
+      }
+      float best[U];
+#pragma unroll
+      for (int j = 0; j < U; ++j) best[j] = -INFINITY;
+      for (int h = 0; h < G; ++h) {
+        const float4 q = *(const float4*)(qs + h * D + c * 4);
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          float s = q.x * k[j].x;
+          s = fmaf(q.y, k[j].y, s);
+          s = fmaf(q.z, k[j].z, s);
+          s = fmaf(q.w, k[j].w, s);
+          best[j] = fmaxf(best[j], group_sum<LPK>(s));
         }
       }
-      best = fmaxf(best, acc);
+      // lane c of a key group writes the key of load c
+      float v = best[0];
+#pragma unroll
+      for (int j = 1; j < U; ++j) v = c == j ? best[j] : v;
+      const int i = r0 + t + c * KPI + sub;
+      if (c < U && i < end) {
+        const uint32_t key = score_key((ok >> c) & 1u ? v : 0.f);
+        keys[i] = key;
+        if (HIST) atomicAdd(&hist[key >> 21], 1u);
+      }
     }
-    const uint32_t key = score_key(best);
-    keys[i] = key;
-    if (HIST) atomicAdd(&hist[key >> 21], 1u);
   }
-  __syncthreads();
-  if (HIST) flush_hist(hist, a.hist0 + (size_t)row * kHistBins);
+  if (HIST) {
+    __syncthreads();
+    flush_hist(hist, a.hist0 + (size_t)row * kHistBins);
+  }
 }
 
 // Level-0 split of a chunk of keys: keys above the threshold bin are
@@ -1952,6 +1986,7 @@ hipError_t launch_select(const SelectLaunch& s, hipStream_t stream) {
   const int mid_max = a.mcap;
   const bool radix = path == SelPath::kRadix;
   const dim3 sgrid((mid_max + kScoreChunk - 1) / kScoreChunk, rows);
+  const dim3 fgrid32((mid_max + kScoreChunkF32 - 1) / kScoreChunkF32, rows);
 #define PRHS_SCORE_LAUNCH(HIST)                                                               \
   if (s.dtype == 1) {                                                                         \
     const bool paged = s.kv.paged != 0;                                                       \
@@ -1963,8 +1998,8 @@ hipError_t launch_select(const SelectLaunch& s, hipStream_t stream) {
       else hipLaunchKernelGGL((score_bf16<64, false, HIST>), sgrid, dim3(kScoreBlock), 0, stream, a);        \
     }                                                                                         \
   } else {                                                                                    \
-    if (s.kv.d == 128) hipLaunchKernelGGL((score_f32<128, HIST>), sgrid, dim3(kScoreBlock), 0, stream, a);   \
-    else hipLaunchKernelGGL((score_f32<64, HIST>), sgrid, dim3(kScoreBlock), 0, stream, a);                  \
+    if (s.kv.d == 128) hipLaunchKernelGGL((score_f32<128, HIST>), HIST ? sgrid : fgrid32, dim3(kScoreBlock), 0, stream, a); \
+    else hipLaunchKernelGGL((score_f32<64, HIST>), HIST ? sgrid : fgrid32, dim3(kScoreBlock), 0, stream, a);                \
   }
   if (radix) {
     PRHS_SCORE_LAUNCH(true)

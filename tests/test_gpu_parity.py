@@ -864,3 +864,42 @@ def test_select_off_grid_within_rounding_of_threshold(name):
             R = O.reuse_set(own, m, p.dilate_r, n0, n0, p.sink, p.window)
             assert hlen[b, g] == len(R) and np.array_equal(hidx[b, g, : len(R)], R)
     print(f"{name}: {swaps} positions swapped at a threshold")
+
+
+# ---------------------------------------------------------------- fp32 groups
+
+F32_GROUPS = [
+    # hq, hkv, d, paged, lens: query groups of every size class of the fp32
+    # kernels (1, 2, up to 4, up to 8, two workgroups of up to 8), lengths
+    # around their steps (8 or 16 rows), splits (64 rows) and wave runs (64 keys)
+    (2, 2, 128, False, (1, 7, 63, 65)),
+    (6, 2, 128, True, (16, 255, 257, 2049)),
+    (5, 1, 64, False, (64, 1023, 1025)),
+    (8, 1, 128, False, (129, 300)),
+    (18, 2, 64, True, (500, 77)),
+    (16, 1, 128, False, (33, 700)),
+]
+
+
+@pytest.mark.parametrize("hq,hkv,d,paged,lens", F32_GROUPS)
+def test_f32_query_groups(hq, hkv, d, paged, lens):
+    # grid inputs: scores are exact in fp32, the selections are the oracle's
+    inp = synth.random_inputs(len(lens), hq, hkv, d, lens, dtype="f32", paged=paged, page_size=8,
+                              seed=301 + hq + d, grid=True, device=DEV)
+    check_select(inp, lens, B.params(k=40, sink=2, window=9))
+    y, lse = run_dense(inp, lens)
+    rng = np.random.default_rng(hq + d)
+    sets = {(b, h): sorted(rng.choice(n, size=int(rng.integers(1, n + 1)), replace=False).tolist())
+            for b, n in enumerate(lens) for h in range(hkv)}
+    z, zse = run_sparse(inp, lens, sets, max(len(s) for s in sets.values()))
+    g = hq // hkv
+    for b, n in enumerate(lens):
+        for hk in range(hkv):
+            K, V = synth.gather_unit(inp, 0, b, hk, n)
+            Qg = synth.query_group(inp, 0, 0, b, hk)
+            for j in range(g):
+                h = hk * g + j
+                yr, lr = O.dense_attention(Qg[j], K, V)
+                assert_close(y[b, h], lse[b, h], yr, lr, TOL["f32"], f"dense b{b} h{h} n{n}")
+                yr, lr = O.sparse_attention(Qg[j], K, V, sets[(b, hk)])
+                assert_close(z[b, h], zse[b, h], yr, lr, TOL["f32"], f"sparse b{b} h{h} n{n}")
