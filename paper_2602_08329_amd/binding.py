@@ -6,12 +6,19 @@ GPU, before its data pointer and the current HIP stream are handed to the C
 ABI (so a wrongly shaped or host tensor raises ValueError instead of reaching
 a kernel).  Every step of the hot path runs in the library's HIP kernels; there
 is no fallback.  ``lib()`` raises when the library has not been built.
+
+The extension ``_prhs_host`` makes the same checks and the call in native code
+(an attention call is enqueued in 4.2 us with it, in 12.9 from Python and
+ctypes).  It answers None where a check does not hold or an argument is of
+another kind (a tensor subclass, a number that is not a plain float or int);
+the Python code below then raises, or makes the call.
 """
 
 from __future__ import annotations
 
 import ctypes
 import os
+from ctypes import addressof
 
 import torch
 
@@ -87,11 +94,20 @@ class PrhsError(RuntimeError):
 
 
 _lib = None
+_host = None   # the native marshalling, bound to _lib
+
+# entry points the extension calls, in the order it takes them
+_HOST_ENTRIES = [
+    "prhs_select", "prhs_select_shared", "prhs_select_gated", "prhs_gate_select",
+    "prhs_dilate_reuse", "prhs_sparse_decode_attn", "prhs_sparse_decode_attn_static",
+    "prhs_reuse_decode_attn", "prhs_dense_decode_attn", "prhs_pool_decode_attn",
+    "prhs_prefill_attn", "prhs_schedule",
+]
 
 
 def lib():
     """The loaded libprhs; raises if it has not been built."""
-    global _lib
+    global _lib, _host
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with "
@@ -146,6 +162,13 @@ def lib():
         L.prhs_psaw_first_visible.argtypes = [P(PrhsPsaw), i32]
         L.prhs_last_error.restype = ctypes.c_char_p
         L.prhs_last_error.argtypes = []
+        try:
+            from . import _prhs_host
+        except ImportError as e:
+            raise RuntimeError("the _prhs_host extension is missing: build it with "
+                               "`python -m paper_2602_08329_amd.build`") from e
+        _prhs_host.bind(*(ctypes.cast(getattr(L, n), vp).value for n in _HOST_ENTRIES))
+        _host = _prhs_host
         _lib = L
     return _lib
 
@@ -185,6 +208,18 @@ def _stream(stream):
     if stream is None:
         stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream)
+
+
+def _handle(stream):
+    """Handle of `stream`, by default the current one of the current GPU."""
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
+
+
+def _native(kv):
+    """Whether a call on this cache may take the native marshalling."""
+    return _host is not None and type(kv) is KV and kv.device.type == "cuda"
 
 
 def _need(t, dtype, name, shape=None, dims=None):
@@ -273,6 +308,10 @@ def prhs_set_capacity(p, max_seq_len):
 
 
 def prhs_schedule(step, layer, p):
+    if _host is not None and type(p) is PrhsParams:
+        r = _host.schedule(step, layer, addressof(p))
+        if r is not None:
+            return r
     return lib().prhs_schedule(step, layer, ctypes.byref(p))
 
 
@@ -330,6 +369,11 @@ def _selection_outputs(kv, topk_idx, topk_len, set_idx, set_len, shared_idx=None
 
 
 def prhs_select(kv, q, p, topk_idx, topk_len, set_idx, set_len, ws, stream=None):
+    if _native(kv) and type(p) is PrhsParams:
+        st = _host.select(addressof(kv.c), kv._keep, kv.device.index, q, addressof(p),
+                          topk_idx, topk_len, set_idx, set_len, ws, _handle(stream))
+        if st is not None:
+            return check(st)
     _q(kv, q)
     _selection_outputs(kv, topk_idx, topk_len, set_idx, set_len)
     _ws(ws)
@@ -344,6 +388,12 @@ def prhs_select_shared(kv, q, p, topk_idx, topk_len, set_idx, set_len, shared_id
                        stream=None):
     """prhs_select that also writes the dilated shared set at the anchor
     length (shared_idx has the same capacity as set_idx)."""
+    if _native(kv) and type(p) is PrhsParams:
+        st = _host.select_shared(addressof(kv.c), kv._keep, kv.device.index, q,
+                                 addressof(p), topk_idx, topk_len, set_idx, set_len, shared_idx,
+                                 shared_len, ws, _handle(stream))
+        if st is not None:
+            return check(st)
     _q(kv, q)
     _selection_outputs(kv, topk_idx, topk_len, set_idx, set_len, shared_idx, shared_len)
     _ws(ws)
@@ -356,6 +406,12 @@ def prhs_select_shared(kv, q, p, topk_idx, topk_len, set_idx, set_len, shared_id
 
 
 def prhs_dilate_reuse(p, topk_idx, topk_len, anchor_lens, seq_lens, set_idx, set_len, stream=None):
+    if (_host is not None and type(p) is PrhsParams and isinstance(topk_idx, torch.Tensor)
+            and topk_idx.is_cuda):
+        st = _host.dilate_reuse(addressof(p), topk_idx, topk_len, anchor_lens, seq_lens, set_idx,
+                                set_len, _handle(stream))
+        if st is not None:
+            return check(st)
     _need(topk_idx, torch.int32, "topk_idx", dims=3)
     B, Hkv, k_cap = topk_idx.shape
     _need(topk_len, torch.int32, "topk_len", shape=(B, Hkv))
@@ -378,6 +434,11 @@ def _sets(kv, set_idx, set_len):
 
 
 def prhs_sparse_decode_attn(kv, q, set_idx, set_len, scale, out, lse, ws, stream=None):
+    if _native(kv) and ws is not None:
+        st = _host.sparse(addressof(kv.c), kv._keep, kv.device.index, q, set_idx,
+                          set_len, scale, out, lse, ws, _handle(stream))
+        if st is not None:
+            return check(st)
     _q(kv, q)
     _sets(kv, set_idx, set_len)
     _outputs(kv, out, lse)
@@ -392,6 +453,11 @@ def prhs_sparse_decode_attn_static(kv, q, set_idx, set_len, scale, out, lse, str
     """prhs_sparse_decode_attn with its split-K partials in the library's
     static device array instead of a workspace: no allocation anywhere.
     Calls that overlap on one GPU race."""
+    if _native(kv):
+        st = _host.sparse(addressof(kv.c), kv._keep, kv.device.index, q, set_idx,
+                          set_len, scale, out, lse, None, _handle(stream))
+        if st is not None:
+            return check(st)
     _q(kv, q)
     _sets(kv, set_idx, set_len)
     _outputs(kv, out, lse)
@@ -405,6 +471,11 @@ def prhs_reuse_decode_attn(kv, q, set_idx, set_len, anchor_lens, scale, out, lse
                            stream=None):
     """Attention over set U [anchor_lens[b], n_b): the reused set of a later
     step, with the set built once at the anchor length."""
+    if _native(kv):
+        st = _host.reuse(addressof(kv.c), kv._keep, kv.device.index, q, set_idx,
+                         set_len, anchor_lens, scale, out, lse, ws, _handle(stream))
+        if st is not None:
+            return check(st)
     _q(kv, q)
     _sets(kv, set_idx, set_len)
     _need(anchor_lens, torch.int32, "anchor_lens", shape=(kv.c.batch,))
@@ -462,6 +533,13 @@ def prhs_gate_select(kv, q, p, tau, slot, ref_q, ref_valid, slot_lens, choice, r
     """prhs_gate (recording the step) and the refresh of the retrieving units
     in one call; the gate runs inside the refresh launch where that is one
     fused kernel."""
+    if _native(kv) and type(p) is PrhsParams:
+        st = _host.gate_select(addressof(kv.c), kv._keep, kv.device.index, q,
+                               addressof(p), tau, slot, ref_q, ref_valid, slot_lens, choice,
+                               row_anchor, row_other, tail, topk_idx, topk_len, set_idx, set_len,
+                               shared_idx, shared_len, ws, _handle(stream))
+        if st is not None:
+            return check(st)
     _q(kv, q)
     seq_lens = kv._keep[2]
     S = _gate_arrays(q, seq_lens, ref_q, ref_valid, slot_lens, choice, row_anchor, row_other, tail,
@@ -483,6 +561,12 @@ def prhs_gate_select(kv, q, p, tau, slot, ref_q, ref_valid, slot_lens, choice, r
 def prhs_select_gated(kv, q, p, choice, topk_idx, topk_len, set_idx, set_len, shared_idx, shared_len,
                       ws, stream=None):
     """prhs_select_shared for the units with choice < 0 only."""
+    if _native(kv) and type(p) is PrhsParams:
+        st = _host.select_gated(addressof(kv.c), kv._keep, kv.device.index, q,
+                                addressof(p), choice, topk_idx, topk_len, set_idx, set_len,
+                                shared_idx, shared_len, ws, _handle(stream))
+        if st is not None:
+            return check(st)
     _q(kv, q)
     _need(choice, torch.int32, "choice", shape=(kv.units,))
     _selection_outputs(kv, topk_idx, topk_len, set_idx, set_len, shared_idx, shared_len)
@@ -504,6 +588,13 @@ def prhs_pool_decode_attn(kv, q, pool_idx, pool_len, unit_row, unit_tail, scale,
     to rows), pool_len with the same leading dims.  units_side (with the
     gate's choice as unit_gate) restricts the launch to the retrieving or
     the sharing units; the others' outputs are left as they are."""
+    if _native(kv) and (psaw is None or type(psaw) is PrhsPsaw):
+        st = _host.pool(addressof(kv.c), kv._keep, kv.device.index, q, pool_idx,
+                        pool_len, unit_row, unit_tail, unit_gate, units_side,
+                        None if psaw is None else addressof(psaw), scale, out, lse, ws,
+                        _handle(stream))
+        if st is not None:
+            return check(st)
     if units_side != PRHS_UNITS_ALL:
         _need(unit_gate, torch.int32, "unit_gate", shape=(kv.units,))
     _q(kv, q)
@@ -532,6 +623,11 @@ def prhs_prefill_attn(kv, q, scale, out, lse=None, psaw=None, stream=None):
     """Causal prefill attention of the prompts (kv holds them; seq_lens are
     their lengths) for the queries q [B][Hq][T][d] at positions 0 .. T - 1,
     under the layer's PSAW mask (Eq. psaw) when psaw (a PrhsPsaw) is given."""
+    if _native(kv) and (psaw is None or type(psaw) is PrhsPsaw):
+        st = _host.prefill(addressof(kv.c), kv._keep, kv.device.index, q, scale, out, lse,
+                           None if psaw is None else addressof(psaw), _handle(stream))
+        if st is not None:
+            return check(st)
     _need(q, kv.dtype, "q", dims=4)
     B_, H_, T, d = q.shape
     _need(q, kv.dtype, "q", shape=(kv.c.batch, kv.c.num_q_heads, T, kv.c.head_dim))
@@ -546,6 +642,11 @@ def prhs_prefill_attn(kv, q, scale, out, lse=None, psaw=None, stream=None):
 
 
 def prhs_dense_decode_attn(kv, q, scale, out, lse, ws, stream=None):
+    if _native(kv):
+        st = _host.dense(addressof(kv.c), kv._keep, kv.device.index, q, scale, out, lse, ws,
+                         _handle(stream))
+        if st is not None:
+            return check(st)
     _q(kv, q)
     _outputs(kv, out, lse)
     _ws(ws)

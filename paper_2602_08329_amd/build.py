@@ -1,4 +1,5 @@
-"""Builds libprhs.so (HIP for gfx950) in-tree with hipcc.
+"""Builds libprhs.so (HIP for gfx950) in-tree with hipcc, and the CPython
+extension _prhs_host.so (the binding's marshalling, no device code) with g++.
 
     python -m paper_2602_08329_amd.build [-v]
     python -m paper_2602_08329_amd.build --host-sanitize OUT.so
@@ -17,6 +18,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -25,6 +27,9 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libprhs.so")
 SOURCES = ["prhs_api.hip", "select.hip", "dilate.hip", "attention.hip", "gate.hip", "prefill.hip"]
+
+HOST_SOURCE = "host_binding.cpp"
+HOST_LIB = os.path.join(PKG, "_prhs_host.so")
 
 ARCH = "gfx950"
 FLAGS = [
@@ -53,6 +58,23 @@ SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=unde
             "-Xarch_host", "-fno-omit-frame-pointer", "-g"]
 
 
+def host_command(out):
+    """The g++ line of the binding's extension, against torch's headers and the
+    libraries `import torch` has loaded."""
+    import torch
+    from torch.utils import cpp_extension
+    cc = shutil.which("g++")
+    if cc is None:
+        raise RuntimeError("g++ not found; the binding's extension cannot be built")
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    inc = [x for p in cpp_extension.include_paths() for x in ("-isystem", p)]
+    return [cc, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc,
+            "-I", sysconfig.get_paths()["include"], "-I", INCLUDE,
+            os.path.join(CSRC, HOST_SOURCE), "-o", out, "-L", lib, "-ltorch_python", "-ltorch_cpu",
+            "-lc10"]
+
+
 def build(verbose: bool = False, host_sanitize: str = None) -> str:
     out_lib = LIB if host_sanitize is None else os.path.abspath(host_sanitize)
     objdir = BUILD if host_sanitize is None else out_lib + ".objs"
@@ -74,6 +96,13 @@ def build(verbose: bool = False, host_sanitize: str = None) -> str:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
                                             text=True)))
+    host_tmp = HOST_LIB + ".tmp"
+    if host_sanitize is None:
+        cmd = host_command(host_tmp)
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        procs.append((HOST_SOURCE, subprocess.Popen(cmd, stdout=subprocess.PIPE,
+                                                    stderr=subprocess.STDOUT, text=True)))
     errors = []
     for src, p in procs:
         out, _ = p.communicate()
@@ -92,6 +121,8 @@ def build(verbose: bool = False, host_sanitize: str = None) -> str:
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout)
     os.replace(tmp, out_lib)
+    if host_sanitize is None:
+        os.replace(host_tmp, HOST_LIB)
     return out_lib
 
 

@@ -94,6 +94,11 @@ class DecodeRunner:
         self.shared_set = torch.zeros(G_, Bsz, w.hkv, self.set_cap, dtype=i32, device=dev)
         self.shared_len = torch.zeros(G_, Bsz, w.hkv, dtype=i32, device=dev)
         self.anchor_step = [None] * G_
+        # the groups' and steps' views of the state above, made once
+        self.lens_at = list(self.seq_lens.unbind(0))
+        self.topk_of = list(zip(self.topk_idx.unbind(0), self.topk_len.unbind(0)))
+        self.anchor_of = list(zip(self.anchor_set.unbind(0), self.anchor_len.unbind(0)))
+        self.shared_of = list(zip(self.shared_set.unbind(0), self.shared_len.unbind(0)))
         kv0 = self.kv[0][0]
         self.ws_select = B.workspace(B.prhs_workspace_size(B.PRHS_OP_SELECT, kv0, self.params), dev)
         self.ws_attn = B.workspace(
@@ -123,13 +128,11 @@ class DecodeRunner:
     def refresh(self, gi, j):
         l = gi * self.w.G
         if self.per_step_sets or not self.reuses:
-            B.prhs_select(self.kv[l][j], self.inp.q[l, j], self.params, self.topk_idx[gi],
-                          self.topk_len[gi], self.anchor_set[gi], self.anchor_len[gi],
-                          self.ws_select)
+            B.prhs_select(self.kv[l][j], self.inp.q[l, j], self.params, *self.topk_of[gi],
+                          *self.anchor_of[gi], self.ws_select)
         else:
-            B.prhs_select_shared(self.kv[l][j], self.inp.q[l, j], self.params, self.topk_idx[gi],
-                                 self.topk_len[gi], self.anchor_set[gi], self.anchor_len[gi],
-                                 self.shared_set[gi], self.shared_len[gi], self.ws_select)
+            B.prhs_select_shared(self.kv[l][j], self.inp.q[l, j], self.params, *self.topk_of[gi],
+                                 *self.anchor_of[gi], *self.shared_of[gi], self.ws_select)
         self.anchor_step[gi] = j
 
     def _anchor(self, gi, j):
@@ -140,9 +143,9 @@ class DecodeRunner:
 
     def share(self, gi, j):
         j0 = self._anchor(gi, j)
-        n = self.seq_lens[j] if self.per_step_sets else self.seq_lens[j0]
-        B.prhs_dilate_reuse(self.params, self.topk_idx[gi], self.topk_len[gi], self.seq_lens[j0],
-                            n, self.shared_set[gi], self.shared_len[gi])
+        n = self.lens_at[j] if self.per_step_sets else self.lens_at[j0]
+        B.prhs_dilate_reuse(self.params, *self.topk_of[gi], self.lens_at[j0], n,
+                            *self.shared_of[gi])
 
     def shares_at(self, j):
         """Groups whose shared set prhs_dilate_reuse (re)builds at step j (in
@@ -157,10 +160,10 @@ class DecodeRunner:
         set[:len], then [tail_start[b], n_b) when tail_start is not None."""
         gi = l // self.w.G
         if B.prhs_schedule(j, l, self.params) == B.PRHS_REFRESH:
-            return self.anchor_set[gi], self.anchor_len[gi], None
+            return (*self.anchor_of[gi], None)
         j0 = self._anchor(gi, j)
-        tail = None if self.per_step_sets else self.seq_lens[j0]
-        return self.shared_set[gi], self.shared_len[gi], tail
+        tail = None if self.per_step_sets else self.lens_at[j0]
+        return (*self.shared_of[gi], tail)
 
     def attend(self, l, j, out=None, lse=None):
         s, n, tail = self.set_for(l, j)
