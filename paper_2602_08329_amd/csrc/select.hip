@@ -6,13 +6,13 @@
 // gate sends to retrieval.
 //
 // Three paths, all on the caller's stream (select_path picks one):
-//   select_fused   middle range within LDS, contiguous bf16, rows filling
-//                  more than half the CUs: one workgroup per row scores into
+//   select_fused   middle range within LDS, bf16, rows filling more than half
+//                  the CUs (or very short): one workgroup per row scores into
 //                  LDS, takes exact thresholds for k and m over the 32-bit
 //                  keys and compacts in position order (which settles ties)
 //                  -- one launch;
-//   keyed path     middle range within LDS, fewer rows (or a paged or fp32
-//                  cache): score_* without histograms spreads each row over
+//   keyed path     middle range within LDS, fewer rows (or an fp32 cache):
+//                  score_* without histograms spreads each row over
 //                  many workgroups and writes its keys, then select_keyed
 //                  runs select_fused's selection half, one workgroup per row
 //                  -- two launches;
@@ -46,6 +46,7 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kScoreBlock = 256;
 constexpr int kScoreChunk = 1024;   // keys per score workgroup
+constexpr int kScoreChunkMin = 128; // 32 keys per wave
 constexpr int kScoreChunkF32 = 256; // the same of score_f32 without histograms
 constexpr int kScoreSub = 2;        // 16-key sub-tiles per wave step of score_bf16
 constexpr int kFilterBlock = 256;
@@ -72,6 +73,8 @@ struct SelArgs {
   const void* q;
   int k, k_num, k_den, sink, window, dilate_m;
   int mcap, selcap;
+  int score_chunk;     // keys per workgroup of score_bf16
+  int page_shift;      // log2 of the page size, -1 when it is no power of two
   int sortcap;         // LDS sort buffer entries of select_finish (>= selcap)
   int stagecap;        // LDS output staging entries of select_finish
   int woff;            // select_finish has LDS for per-word output offsets
@@ -245,6 +248,22 @@ __device__ __forceinline__ void score_load(ScoreStep<D, SUB>& S, const SelArgs& 
     }
 }
 
+// The same 16 SUB <= 64 keys from their row ids (-1: none), key i's in lane i.
+template <int D, int SUB>
+__device__ __forceinline__ void score_load_ids(ScoreStep<D, SUB>& S, const SelArgs& a, int32_t ids,
+                                               int lane) {
+  constexpr int CH = D / 8, RPI = 64 / CH;
+  const __bf16* kbase = (const __bf16*)a.kv.k;
+  const int kc = lane % CH, kr = lane / CH;
+#pragma unroll
+  for (int s = 0; s < SUB; ++s)
+#pragma unroll
+    for (int j = 0; j < D / 32; ++j) {
+      const int32_t row = __shfl(ids, s * 16 + j * RPI + kr);
+      S.kraw[s][j] = stream_load16(kbase + (int64_t)(row < 0 ? 0 : row) * D + kc * 8);
+    }
+}
+
 // kst: the wave's LDS tile of 16 x d bf16.  LDS operations of one wave
 // complete in order; the wave barriers keep the compiler from moving them
 // across each other.
@@ -307,9 +326,9 @@ __global__ __launch_bounds__(kScoreBlock) __attribute__((amdgpu_waves_per_eu(4))
   if (row_skipped(a, row)) return;
   const int b = row / a.kv.hkv, g = row % a.kv.hkv;
   const RowGeom rg = row_geom(a, b);
-  const int base = blockIdx.x * kScoreChunk;
+  const int base = blockIdx.x * a.score_chunk;
   if (base >= rg.m || rg.kb <= 0) return;
-  const int end = min(rg.m, base + kScoreChunk);
+  const int end = min(rg.m, base + a.score_chunk);
   for (int i = threadIdx.x; i < kHistBins; i += kScoreBlock) hist[i] = 0u;
   int p0 = 0;
   if (PAGED) {
@@ -1336,6 +1355,7 @@ __device__ __forceinline__ uint64_t lowest_bits(uint64_t x, uint32_t t) {
   return r;
 }
 
+constexpr int kShortKeyed = 6144;            // longest rows select_keyed takes with 512 threads
 constexpr int kFusedMaxKeys = 24576;         // middle range held in LDS (96 KB)
 constexpr int kBmWords = kFusedMaxKeys / 32;  // words of a bitmap over the middle range
 static_assert(2 * kBmWords <= kHistBins, "two selection bitmaps in the histogram");
@@ -1486,7 +1506,7 @@ __device__ __forceinline__ void build_bitmaps(const uint32_t* s_keys, int M, int
 // level-0 histogram, then the selection half below (exact thresholds for
 // the k_b and m largest, the selections as position-ordered bitmaps, which
 // also settle ties): top m, other winners, anchor set, shared set.
-// Contiguous bf16 caches whose middle range fits LDS.
+// bf16 caches whose middle range fits LDS.
 // Row of fused-refresh workgroup w when there are more rows than CUs: rows
 // by decreasing length.  One workgroup per CU: the workgroups that start
 // last, as earlier ones finish, carry the shortest rows (longest-first
@@ -1680,7 +1700,7 @@ __device__ void fused_select_tail(const SelArgs& a, int row, const RowGeom& rg, 
   }
 }
 
-template <int D, int BLOCK>
+template <int D, int BLOCK, bool PAGED>
 __global__ __launch_bounds__(BLOCK) void select_fused(SelArgs a) {
   constexpr int KS = D / 32;
   extern __shared__ __attribute__((aligned(16))) uint32_t s_keys[];  // [middle length]
@@ -1729,20 +1749,44 @@ __global__ __launch_bounds__(BLOCK) void select_fused(SelArgs a) {
     constexpr int kStride = 32 * (BLOCK / 64);
     const int t0 = wave * 32;
     const int iters = t0 < M ? (M - t0 + kStride - 1) / kStride : 0;
+    // Paged: lane l resolves key t + l % 32 through the block table, two
+    // steps ahead and before the K loads of the step between, since loads
+    // complete in order.
+    auto ids_of = [&](int t) -> int32_t {
+      const int i = t + (lane & 31);
+      if (i >= M) return -1;
+      const int pos = rg.sink_end + i, ps = a.kv.page_size;
+      const int page = a.page_shift >= 0 ? pos >> a.page_shift : pos / ps;
+      if (page >= a.kv.max_pages) return -1;
+      const int phys = a.kv.table[(int64_t)b * a.kv.max_pages + page];
+      if (phys < 0 || phys >= a.kv.num_pages) return -1;
+      return (phys * a.kv.hkv + g) * ps + (pos - page * ps);
+    };
+    int32_t ids = PAGED ? ids_of(t0) : 0, next = PAGED ? ids_of(t0 + kStride) : 0;
+    auto load = [&](ScoreStep<D, 2>& S, int t) {
+      if constexpr (PAGED) {
+        const int32_t ahead = ids_of(t + 2 * kStride);
+        score_load_ids<D>(S, a, ids, lane);
+        ids = next;
+        next = ahead;
+      } else {
+        score_load<D, false>(S, a, rg, b, g, t, M, 0, nullptr, lane);
+      }
+    };
     if (iters > 0) {
       ScoreStep<D, 2> A, B;
       int t = t0;
-      score_load<D, false>(A, a, rg, b, g, t, M, 0, nullptr, lane);
+      load(A, t);
       int i = 0;
       for (; i + 2 < iters; i += 2) {
-        score_load<D, false>(B, a, rg, b, g, t + kStride, M, 0, nullptr, lane);
+        load(B, t + kStride);
         score_consume<D>(A, qf, G, gp, t, M, lane, s_keys, h, s_kst[wave]);
-        score_load<D, false>(A, a, rg, b, g, t + 2 * kStride, M, 0, nullptr, lane);
+        load(A, t + 2 * kStride);
         score_consume<D>(B, qf, G, gp, t + kStride, M, lane, s_keys, h, s_kst[wave]);
         t += 2 * kStride;
       }
       if (i + 1 < iters) {
-        score_load<D, false>(B, a, rg, b, g, t + kStride, M, 0, nullptr, lane);
+        load(B, t + kStride);
         score_consume<D>(A, qf, G, gp, t, M, lane, s_keys, h, s_kst[wave]);
         score_consume<D>(B, qf, G, gp, t + kStride, M, lane, s_keys, h, s_kst[wave]);
       } else {
@@ -1823,12 +1867,19 @@ namespace {
 enum class SelPath { kFused, kKeyed, kRadix };
 
 // The refresh's launch sequence.  Middle ranges that fit LDS: one fused
-// launch when the rows (one workgroup each) fill more than half the CUs and
-// the cache is contiguous bf16, else scoring spread over many workgroups per
-// row followed by one selection workgroup per row (keyed).  Longer middle
-// ranges: the radix path (clear, score, filter, finish).
+// launch when the rows (one workgroup each) fill more than half the CUs, or
+// are so short (kFusedShortBytes of K) that a launch of their own costs more
+// than reading them by one workgroup each, and the cache is bf16; else scoring
+// spread over many workgroups per row followed by one selection workgroup per
+// row (keyed).  Longer middle ranges: the radix path (score, filter, finish).
+// Fused / keyed, us: 4 rows of 400 keys at d 64 11.2 / 12.7, of 1000 13.7 /
+// 13.4; 128 rows of 400 at d 128 15.7 / 16.3, of 1000 20.7 / 19.9; 152 rows of
+// 1000 20.8 / 22.1, of 4000 43.4 / 41.8; 256 of 4000 56.4 / 58.5; paged, 16
+// tokens a page, 384 rows of 4k to 8k 120 / 143, 512 of 8k to 16k 283 / 316,
+// 512 of 500 to 1000 30.9 / 37.6 (350 and 46 before the paged form).
 // PRHS_SELECT_PATH=fused|keyed|split forces a path where it applies.
-SelPath select_path(int dtype, bool paged, int rows, int mcap) {
+constexpr long long kFusedShortBytes = 100 * 1024;
+SelPath select_path(int dtype, int d, int rows, int mcap) {
   static const int force = [] {
     const char* e = getenv("PRHS_SELECT_PATH");
     if (!e) return 0;
@@ -1838,13 +1889,14 @@ SelPath select_path(int dtype, bool paged, int rows, int mcap) {
     return 0;
   }();
   const bool fits = mcap <= kFusedMaxKeys;
-  const bool fused_ok = fits && dtype == 1 && !paged;
+  const bool fused_ok = fits && dtype == 1;
   if (force == 1 && fused_ok) return SelPath::kFused;
   if (force == 2 && fits) return SelPath::kKeyed;
   if (force == 3) return SelPath::kRadix;
   if (!fits) return SelPath::kRadix;
   const int cus = device_cus();
-  if (fused_ok && (cus <= 0 || 2 * rows > cus)) return SelPath::kFused;
+  if (fused_ok && (cus <= 0 || 2 * rows > cus || (long long)mcap * d * 2 <= kFusedShortBytes))
+    return SelPath::kFused;
   return SelPath::kKeyed;
 }
 
@@ -1924,8 +1976,10 @@ hipError_t launch_select(const SelectLaunch& s, hipStream_t stream) {
   a.seg_shift = 0;
   a.row_choice = s.row_choice;
   a.gate_fused = 0;
+  const int ps = s.kv.page_size;
+  a.page_shift = ps > 0 && (ps & (ps - 1)) == 0 ? __builtin_ctz(ps) : -1;
 
-  const SelPath path = select_path(s.dtype, s.kv.paged != 0, rows, a.mcap);
+  const SelPath path = select_path(s.dtype, s.kv.d, rows, a.mcap);
   if (s.gate) {
     if (path == SelPath::kFused) {
       a.gate_fused = 1;   // the gate runs inside the refresh launch
@@ -1947,45 +2001,53 @@ hipError_t launch_select(const SelectLaunch& s, hipStream_t stream) {
     // two to a CU, so that one's selection overlaps the other's scoring.
     // Either way only while the workgroup's LDS (static part plus the key
     // array) fits the CU's 160 KB.
+    const bool paged = s.kv.paged != 0;
+    const void* narrow_fn = s.kv.d == 128 ? (paged ? (const void*)select_fused<128, 512, true>
+                                                   : (const void*)select_fused<128, 512, false>)
+                                          : (paged ? (const void*)select_fused<64, 512, true>
+                                                   : (const void*)select_fused<64, 512, false>);
+    const void* wide_fn = s.kv.d == 128 ? (paged ? (const void*)select_fused<128, 1024, true>
+                                                 : (const void*)select_fused<128, 1024, false>)
+                                        : (paged ? (const void*)select_fused<64, 1024, true>
+                                                 : (const void*)select_fused<64, 1024, false>);
     bool wide = a.balance_cus <= 0 || rows <= a.balance_cus;
     if (!wide) {
       hipFuncAttributes fb;
-      const hipError_t eb =
-          s.kv.d == 128 ? hipFuncGetAttributes(&fb, (const void*)select_fused<128, 512>)
-                        : hipFuncGetAttributes(&fb, (const void*)select_fused<64, 512>);
+      const hipError_t eb = hipFuncGetAttributes(&fb, narrow_fn);
       if (eb != hipSuccess) return eb;
       wide = 2 * (fb.sharedSizeBytes + dyn) > (size_t)kLdsBytes;
     }
     if (wide) {
       hipFuncAttributes fa;
-      const hipError_t ea =
-          s.kv.d == 128 ? hipFuncGetAttributes(&fa, (const void*)select_fused<128, 1024>)
-                        : hipFuncGetAttributes(&fa, (const void*)select_fused<64, 1024>);
+      const hipError_t ea = hipFuncGetAttributes(&fa, wide_fn);
       if (ea != hipSuccess) return ea;
       wide = fa.sharedSizeBytes + dyn <= (size_t)kLdsBytes;
     }
     a.balance_serpentine = wide ? 0 : 1;
     hipError_t e = hipSuccess;
-#define PRHS_FUSED_LAUNCH(DV, BL)                                                           \
-  {                                                                                         \
-    if (dyn > 65536)                                                                        \
-      e = hipFuncSetAttribute((const void*)select_fused<DV, BL>,                             \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);        \
-    if (e == hipSuccess)                                                                    \
-      hipLaunchKernelGGL((select_fused<DV, BL>), dim3(rows), dim3(BL), dyn, stream, a);     \
-  }
-    if (s.kv.d == 128) {
-      if (wide) PRHS_FUSED_LAUNCH(128, 1024) else PRHS_FUSED_LAUNCH(128, 512)
-    } else {
-      if (wide) PRHS_FUSED_LAUNCH(64, 1024) else PRHS_FUSED_LAUNCH(64, 512)
+    if (dyn > 65536)
+      e = hipFuncSetAttribute(wide ? wide_fn : narrow_fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+    if (e == hipSuccess) {
+      void* args[] = {&a};
+      e = hipLaunchKernel(wide ? wide_fn : narrow_fn, dim3(rows), dim3(wide ? 1024 : 512), args, dyn, stream);
     }
-#undef PRHS_FUSED_LAUNCH
     return e != hipSuccess ? e : hipGetLastError();
   }
   // the middle range is shorter than max_seq_len; size grids by max_seq_len
   const int mid_max = a.mcap;
   const bool radix = path == SelPath::kRadix;
-  const dim3 sgrid((mid_max + kScoreChunk - 1) / kScoreChunk, rows);
+  // Keys per scoring workgroup: kScoreChunk with histograms (each workgroup
+  // flushes its own); without, one 32-key step per wave while that gives at
+  // most 8 workgroups per CU, else two (keyed path, d 128, 1024 / 256 / 128
+  // keys, us: 4 rows of 2000 21.6 / 14.4 / 13.5, 72 of 2000 24.1 / 21.6 / 21.3,
+  // 72 of 8000 46.0 / 42.0 / 43.6, 128 of 16000 115.3 / 108.8 / 108.4).
+  a.score_chunk = kScoreChunk;
+  if (!radix) {
+    const long long one = ((long long)mid_max + kScoreChunkMin - 1) / kScoreChunkMin * rows;
+    a.score_chunk = one <= 8LL * device_cus() ? kScoreChunkMin : 2 * kScoreChunkMin;
+  }
+  const dim3 sgrid((mid_max + a.score_chunk - 1) / a.score_chunk, rows);
+  const dim3 hgrid32((mid_max + kScoreChunk - 1) / kScoreChunk, rows);
   const dim3 fgrid32((mid_max + kScoreChunkF32 - 1) / kScoreChunkF32, rows);
 #define PRHS_SCORE_LAUNCH(HIST)                                                               \
   if (s.dtype == 1) {                                                                         \
@@ -1998,8 +2060,8 @@ hipError_t launch_select(const SelectLaunch& s, hipStream_t stream) {
       else hipLaunchKernelGGL((score_bf16<64, false, HIST>), sgrid, dim3(kScoreBlock), 0, stream, a);        \
     }                                                                                         \
   } else {                                                                                    \
-    if (s.kv.d == 128) hipLaunchKernelGGL((score_f32<128, HIST>), HIST ? sgrid : fgrid32, dim3(kScoreBlock), 0, stream, a); \
-    else hipLaunchKernelGGL((score_f32<64, HIST>), HIST ? sgrid : fgrid32, dim3(kScoreBlock), 0, stream, a);                \
+    if (s.kv.d == 128) hipLaunchKernelGGL((score_f32<128, HIST>), HIST ? hgrid32 : fgrid32, dim3(kScoreBlock), 0, stream, a); \
+    else hipLaunchKernelGGL((score_f32<64, HIST>), HIST ? hgrid32 : fgrid32, dim3(kScoreBlock), 0, stream, a);                \
   }
   if (radix) {
     PRHS_SCORE_LAUNCH(true)
@@ -2008,15 +2070,19 @@ hipError_t launch_select(const SelectLaunch& s, hipStream_t stream) {
   }
 #undef PRHS_SCORE_LAUNCH
   if (!radix) {
-    // keyed: one 1024-thread selection workgroup per row over the keys in LDS
+    // keyed: one selection workgroup per row over the keys in LDS, of 512
+    // threads on short rows (fewer waves at each barrier) and where rows wait
+    // for CUs, else 1024 (4 rows of 1000 keys 19.9 / 20.6 us, of 16000 32.8 /
+    // 29.1; 384 rows of 4000 80.5 / 87.0)
     const size_t dyn = (size_t)a.mcap * 4;
+    const int threads = a.mcap <= kShortKeyed || rows > device_cus() ? 512 : 1024;
+    const void* fn = threads == 512 ? (const void*)select_keyed<512> : (const void*)select_keyed<1024>;
     if (dyn > 65536) {
-      const hipError_t e = hipFuncSetAttribute((const void*)select_keyed<1024>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+      const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(select_keyed<1024>, dim3(rows), dim3(1024), dyn, stream, a);
-    return hipGetLastError();
+    void* args[] = {&a};
+    return hipLaunchKernel(fn, dim3(rows), dim3(threads), args, dyn, stream);
   }
   const dim3 fgrid((mid_max + kFilterChunk - 1) / kFilterChunk, rows);
   hipLaunchKernelGGL(select_filter, fgrid, dim3(kFilterBlock), 0, stream, a);

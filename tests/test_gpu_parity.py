@@ -903,3 +903,66 @@ def test_f32_query_groups(hq, hkv, d, paged, lens):
                 assert_close(y[b, h], lse[b, h], yr, lr, TOL["f32"], f"dense b{b} h{h} n{n}")
                 yr, lr = O.sparse_attention(Qg[j], K, V, sets[(b, hk)])
                 assert_close(z[b, h], zse[b, h], yr, lr, TOL["f32"], f"sparse b{b} h{h} n{n}")
+
+
+# ---------------------------------------------------------------- paged fused refresh
+
+@pytest.mark.parametrize("d,page,hkv", [(128, 16, 1), (64, 7, 2), (128, 1, 1)])
+def test_select_fused_paged(d, page, hkv):
+    # rows filling more than half the CUs of a paged cache: lengths around the
+    # 32-key wave steps and the workgroup's stride, pages of 1, 7 and 16 tokens
+    lens = tuple((5, 31, 69, 70, 71, 582, 583, 1100, 2117)[i % 9] + i // 9 for i in range(140 // hkv + 1))
+    inp = synth.random_inputs(len(lens), 4 * hkv, hkv, d, lens, paged=True, page_size=page,
+                              seed=61 + d + page, grid=True, device=DEV)
+    check_select(inp, lens, B.params(k=40, sink=4, window=34))
+    check_select_shared(inp, lens, B.params(k=40, sink=4, window=34, refresh_every=4))
+
+
+@pytest.mark.parametrize("dtype,d,lens", [
+    ("bf16", 128, (400, 399, 7)),            # one launch: K within 100 KB a row
+    ("bf16", 128, (401, 529, 130, 6144)),    # scoring workgroups of 128 keys, 512-thread selection
+    ("bf16", 64, (6145, 6400)),              # 1024-thread selection
+    ("bf16", 128, tuple(9000 - 70 * i for i in range(32))),   # scoring workgroups of 256 keys
+    ("f32", 64, (400, 6145)),
+])
+def test_select_few_rows_by_length(dtype, d, lens):
+    hkv = 1 if len(lens) < 10 else 2
+    inp = synth.random_inputs(len(lens), 2 * hkv, hkv, d, lens, dtype=dtype, seed=71 + len(lens),
+                              grid=True, device=DEV)
+    check_select(inp, lens, B.params(k=60, sink=4, window=16))
+
+
+@pytest.mark.parametrize("paged", [False, True])
+def test_gate_select_short_rows_and_paged_equals_separate_launches(paged):
+    # rows that now take the gate inside one fused launch: few short ones, and
+    # many of a paged cache
+    lens = tuple(200 + i for i in range(3)) if not paged else tuple(900 - 3 * i for i in range(70))
+    inp = synth.random_inputs(len(lens), 8, 2, 64, lens, paged=paged, page_size=16, seed=83,
+                              grid=True, steps=2, device=DEV)
+    n = len(lens)
+    p = B.params(k=30, sink=4, window=8, refresh_every=2)
+    kc, sc = B.prhs_max_topk(p, inp.w.capacity), B.prhs_set_capacity(p, inp.w.capacity)
+    i32 = dict(dtype=torch.int32, device=DEV)
+
+    def state():
+        return ([torch.zeros(2, n, 8, 64, dtype=torch.bfloat16, device=DEV), torch.zeros(2, 2 * n, **i32),
+                 torch.zeros(2, n, **i32)] + [torch.zeros(2 * n, **i32) for _ in range(4)],
+                [torch.full((n, 2, kc), -7, **i32), torch.zeros(n, 2, **i32),
+                 torch.full((n, 2, sc), -7, **i32), torch.zeros(n, 2, **i32),
+                 torch.full((n, 2, sc), -7, **i32), torch.zeros(n, 2, **i32)])
+
+    (g0, s0), (g1, s1) = state(), state()
+    for j in range(2):
+        kv, t = kv_for(inp, [x + j for x in lens])
+        ws = B.workspace(B.prhs_workspace_size(B.PRHS_OP_SELECT, kv, p), DEV)
+        # half the queries of the second step stay close to the first's
+        q = inp.q[0, j].clone()
+        if j == 1:
+            q[::2] = inp.q[0, 0][::2]
+        B.prhs_gate_select(kv, q, p, 0.8, j, *g0, *s0, ws)
+        B.prhs_gate(q, t, 0.8, j, *g1, 2)
+        B.prhs_select_gated(kv, q, p, g1[3], *s1, ws)
+        torch.cuda.synchronize()
+        for x, y in zip(g0 + s0, g1 + s1):
+            assert torch.equal(x, y)
+    assert bool((g0[3] >= 0).any()) and bool((g0[3] < 0).any())
