@@ -909,20 +909,27 @@ __global__ __launch_bounds__(256) void attn_merge(AttnArgs a) {
   }
 }
 
-// Workgroups the split geometry aims for: few for the sparse path (one
-// split per unit avoids the merge launch whenever the units alone fill the
-// chip), many for the dense stream.  PRHS_ATTN_GROUPS and
-// PRHS_ATTN_DENSE_GROUPS override them (tuning knobs, read once per process).
 int env_int(const char* name, int dflt) {
   const char* e = getenv(name);
   const int x = e ? atoi(e) : 0;
   return x > 0 ? x : dflt;
 }
 
-int target_groups(bool dense) {
+// Most workgroups of a launch: one per CU for sets, and for a dense stream
+// short enough that the merge of more splits costs more than it gains (1 x 8
+// units of 4000 rows at d 128 18.1 us with 1024, 10.9 with 256; 16 of 8000
+// 23.4 and 18.9, 4 of 38800 34.8 and 22.5); two, all resident together, for a
+// longer one (8 units of 32000 rows, 131 MB: 256, 512 and 1024 workgroups 33.3,
+// 31.3 and 35.9 us, 80 of 9000 68.5, 65.8 and 67.1).  fp32 dense: below.
+// PRHS_ATTN_GROUPS and PRHS_ATTN_DENSE_GROUPS override them (tuning knobs,
+// read once per process).
+constexpr long long kLongDenseBytes = 96LL << 20;
+long long target_groups(int dtype, bool dense, long long bytes) {
   static const int sparse_v = env_int("PRHS_ATTN_GROUPS", 256);
-  static const int dense_v = env_int("PRHS_ATTN_DENSE_GROUPS", 1024);
-  return dense ? dense_v : sparse_v;
+  static const int dense_v = env_int("PRHS_ATTN_DENSE_GROUPS", 0);
+  if (!dense) return sparse_v;
+  if (dense_v) return dense_v;
+  return dtype != 1 ? 1024 : (bytes < kLongDenseBytes ? 256 : 512);
 }
 
 // Waves per bf16 workgroup: PRHS_ATTN_WAVES overrides the default of 4.
@@ -996,7 +1003,7 @@ AttnLayout attn_layout(int batch, int hq, int d, int nsplit) {
   return L;
 }
 
-int waves_for(int dtype, long long groups, int chunk) {
+int waves_for(int dtype, bool dense, long long groups, int chunk) {
   // fp32: a wave per 16 rows where the workgroups are fewer than two per CU
   // (all rows load at once), else per 32 (less to combine: 1248 units of 60
   // rows 14.1 -> 12.9 us, dense 32 units of 4001 rows 38.8 -> 30.7)
@@ -1004,33 +1011,46 @@ int waves_for(int dtype, long long groups, int chunk) {
     const int rows = groups < 2LL * device_cus() ? 16 : 32;
     return std::min(kMaxWaves, (chunk + rows - 1) / rows);
   }
+  // twice the waves for at least two tiles each while every workgroup has a CU
+  // to itself: more of the set's rows load at once (8 units of 300 rows 8.8 ->
+  // 8.0 us, 16 of 500 11.5 -> 11.0, 72 of 280 at d 64 7.5 -> 7.1; 64 of 200
+  // 8.6 -> 9.0, 384 of 640 30.0 -> 32.9)
   int w = chunk / 32;
-  const int lim = wave_limit();
-  return w < 1 ? 1 : (w > lim ? lim : w);
+  const int lim = wave_limit() * (!dense && groups <= device_cus() && chunk >= 256 ? 2 : 1);
+  return w < 1 ? 1 : std::min({w, lim, kMaxWaves});
 }
 
 }  // namespace
 
 // Rows per workgroup: a multiple of the per-wave tile (32 rows for bf16, 16
-// rows for fp32), sized so about target_groups() workgroups cover the
-// largest unit, at most 8 staged rows per thread, at most kMaxSplits splits,
-// and balanced so the splits of a full unit differ by at most one tile.
-void attn_split_geometry(int dtype, bool dense, int batch, int hq, int hkv, int rows_cap,
+// rows for fp32), so that the launch has at most target_groups() workgroups,
+// at most kMaxSplits splits, and balanced so the splits of a full unit differ
+// by at most one tile.  At most, and not about: 160 units of 800 rows run
+// 25.0 us as 320 workgroups, where some CUs take two, and 19.4 as 160 (192
+// units of 1200 rows 32.6 and 27.3, 80 of 1500 23.3 and 21.2).  Where the
+// rows staged per workgroup, 8 per thread, allow no such split, sets take the
+// fewest splits they allow and a dense stream twice the workgroups and so on
+// (16 units of 65537 rows: 528 workgroups 105 us, 1008 92).
+void attn_split_geometry(int dtype, bool dense, int batch, int hq, int hkv, int d, int rows_cap,
                          int* chunk, int* nsplit) {
   const int gran = dtype == 1 ? 32 : 16;
-  const long long units = (long long)batch * hkv;
+  const long long units = std::max(1LL, (long long)batch * hkv);
   const long long rows = rows_cap > 0 ? rows_cap : 1;
-  const long long tg = target_groups(dense);
-  long long c = (rows * (units > 0 ? units : 1) + tg - 1) / tg;
+  const long long threads = dtype == 1 ? 64LL * wave_limit() : 256;
+  const long long cmax = threads * kRowsPerThread;
+  auto rows_of = [&](long long groups) {
+    const long long k = std::max(1LL, groups / units);
+    return (rows + k - 1) / k;
+  };
+  long long tg = target_groups(dtype, dense, rows * units * d * 4);
+  while (dense && rows_of(tg) > cmax) tg *= 2;
+  long long c = rows_of(tg);
   const long long cmin = (rows + kMaxSplits - 1) / kMaxSplits;
   if (dtype != 1) {
-    const long long fill = (rows * (units > 0 ? units : 1) + 255) / 256;
-    c = std::max(c, std::min((rows + kMergeSplitsF32 - 1) / kMergeSplitsF32, fill));
+    c = std::max(c, std::min((rows + kMergeSplitsF32 - 1) / kMergeSplitsF32, rows_of(256)));
     c = std::max<long long>(c, kMinRowsF32);
   }
   if (c < cmin) c = cmin;
-  const long long threads = dtype == 1 ? 64LL * wave_limit() : 256;
-  const long long cmax = threads * kRowsPerThread;
   if (!dense && rows <= (dtype == 1 ? kNoSplitRows : kNoSplitRowsF32) && rows <= cmax) c = rows;
   if (c > cmax) c = cmax;
   if (c < gran) c = gran;
@@ -1069,7 +1089,7 @@ hipError_t attn_static_scratch(void** ptr) {
 size_t attn_workspace_bytes(int dtype, bool dense, int batch, int hq, int hkv, int d,
                             int rows_cap) {
   int chunk, nsplit;
-  attn_split_geometry(dtype, dense, batch, hq, hkv, rows_cap, &chunk, &nsplit);
+  attn_split_geometry(dtype, dense, batch, hq, hkv, d, rows_cap, &chunk, &nsplit);
   return attn_layout(batch, hq, d, nsplit).total;
 }
 
@@ -1092,7 +1112,7 @@ hipError_t launch_attention(const AttnLaunch& s, bool dense, hipStream_t stream)
   a.set_cap = s.set_cap;
   a.scale_log2 = s.scale * 1.44269504088896340736f;
   const int rows_cap = dense ? s.kv.max_seq_len : s.set_cap;
-  attn_split_geometry(s.dtype, dense, s.kv.batch, s.kv.hq, s.kv.hkv, rows_cap, &a.chunk,
+  attn_split_geometry(s.dtype, dense, s.kv.batch, s.kv.hq, s.kv.hkv, s.kv.d, rows_cap, &a.chunk,
                       &a.nsplit);
   const AttnLayout L = attn_layout(s.kv.batch, s.kv.hq, s.kv.d, a.nsplit);
   char* ws = (char*)s.ws;
@@ -1101,7 +1121,7 @@ hipError_t launch_attention(const AttnLaunch& s, bool dense, hipStream_t stream)
   a.out = s.out;
   a.lse = s.lse;
   const int units = s.kv.batch * s.kv.hkv;
-  const int waves = waves_for(s.dtype, (long long)units * a.nsplit, a.chunk);
+  const int waves = waves_for(s.dtype, dense, (long long)units * a.nsplit, a.chunk);
   const bool paged = s.kv.paged != 0;
 #define PRHS_ATTN_DISPATCH(DV)                                                          \
   if (dense) {                                                                          \

@@ -273,7 +273,7 @@ struct AttnLaunch {
   void* ws;
 };
 // Split geometry shared by workspace sizing and launch.
-void attn_split_geometry(int dtype, bool dense, int batch, int hq, int hkv, int rows_cap,
+void attn_split_geometry(int dtype, bool dense, int batch, int hq, int hkv, int d, int rows_cap,
                          int* chunk, int* nsplit);
 size_t attn_workspace_bytes(int dtype, bool dense, int batch, int hq, int hkv, int d,
                             int rows_cap);

@@ -966,3 +966,39 @@ def test_gate_select_short_rows_and_paged_equals_separate_launches(paged):
         for x, y in zip(g0 + s0, g1 + s1):
             assert torch.equal(x, y)
     assert bool((g0[3] >= 0).any()) and bool((g0[3] < 0).any())
+
+
+# ---------------------------------------------------------------- split geometry
+
+SPLIT_CASES = [
+    # dtype, batch, hq, hkv, d, n, set rows: launches around the lines of the
+    # split rule on 256 CUs
+    ("bf16", 9, 8, 8, 128, 800, 600),      # 72 units: three splits, not four
+    ("bf16", 20, 8, 8, 64, 900, 700),      # 160 units: unsplit although above 512 rows
+    ("bf16", 1, 2, 2, 128, 600, 256),      # few units: eight waves
+    ("bf16", 1, 2, 1, 64, 5000, 4500),     # one unit: rows staged per workgroup bound the split
+    ("f32", 5, 4, 4, 64, 700, 300),
+    ("f32", 1, 1, 1, 128, 2100, 257),
+]
+
+
+@pytest.mark.parametrize("dtype,batch,hq,hkv,d,n,rows", SPLIT_CASES)
+def test_attention_split_geometry(dtype, batch, hq, hkv, d, n, rows):
+    lens = tuple(n - 3 * b for b in range(batch))
+    inp = synth.random_inputs(batch, hq, hkv, d, lens, dtype=dtype, seed=401 + rows, grid=False,
+                              device=DEV)
+    rng = np.random.default_rng(rows)
+    sets = {(b, g): sorted(rng.choice(lens[b], size=rows - (b + g) % 3, replace=False).tolist())
+            for b in range(batch) for g in range(hkv)}
+    y, lse = run_dense(inp, lens)
+    z, zse = run_sparse(inp, lens, sets, rows)
+    gq = hq // hkv
+    for (b, g), S in list(sets.items())[:: max(1, len(sets) // 12)]:
+        K, V = synth.gather_unit(inp, 0, b, g, lens[b])
+        Qg = synth.query_group(inp, 0, 0, b, g)
+        for j in range(gq):
+            h = g * gq + j
+            yr, lr = O.dense_attention(Qg[j], K, V)
+            assert_close(y[b, h], lse[b, h], yr, lr, TOL[dtype], f"dense b{b} h{h}")
+            yr, lr = O.sparse_attention(Qg[j], K, V, S)
+            assert_close(z[b, h], zse[b, h], yr, lr, TOL[dtype], f"sparse b{b} h{h}")
