@@ -38,6 +38,9 @@
 // group's products beside the other's softmax) took the same cycles; dot
 // products for the remainders p - hi were slower, and raised issue priority
 // for the products changed nothing.
+#include <math.h>
+
+#include <algorithm>
 #include <type_traits>
 
 #include "prhs_internal.h"
@@ -54,6 +57,7 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kQueries = 32 * kWaves;  // queries per workgroup with one key side
+constexpr int kPackBlocks = 32;  // blocks a unit up to which a launch's packing is worked out
 constexpr int kXcds = 8;      // accelerator dies, each with its own L2
 constexpr float kLn2 = 0.69314718055994530942f;
 constexpr float kLazyLog2 = 8.f;  // log2 of the largest probability between rescales
@@ -62,6 +66,7 @@ struct PrefillArgs {
   KvView kv;
   const __bf16* q;        // [B][Hq][T][D]
   int T;
+  int qblock;             // queries per workgroup
   int psaw;               // nonzero: row i attends [0, sink) U [first visible at i + 1, i]
   double psaw_f;          // Eq. psaw factor of the layer
   int sink;
@@ -310,7 +315,7 @@ __device__ __forceinline__ void block_of(int units, int nqb, int L, int* bh, int
 
 template <int D, int NS, bool PAGED>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_prefill_bf16(PrefillArgs a) {
-  constexpr int kQBlock = kQueries / NS, QG = kWaves / NS;
+  constexpr int QG = kWaves / NS;           // waves that differ in queries
   constexpr int SUB = NS == 4 ? 1 : 2;      // 32-key sub-tiles per wave and tile
   constexpr int KT = 32 * NS * SUB;         // key rows per tile
   constexpr int KS = D / 16;   // products per 32-key sub-tile of S
@@ -321,7 +326,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   __shared__ float s_ml[NS > 1 ? (NS - 1) * QG : 1][2][64];
   __shared__ int s_vmin;
   __shared__ int64_t s_rows[2][PAGED ? KT : 1];  // paged: row offsets of upcoming tiles
-  const int nqb = (a.T + kQBlock - 1) / kQBlock;
+  const int QB = a.qblock;                  // queries of a block, at most 32 QG
+  const int nqb = (a.T + QB - 1) / QB;
   int bh, qb;
   block_of(a.kv.batch * a.kv.hq, nqb, (int)blockIdx.x, &bh, &qb);
   const int hq = a.kv.hq, G = hq / a.kv.hkv;
@@ -330,20 +336,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, half = lane >> 5;
   const int n = min(kv_seq_len(a.kv, b), a.T);  // prompt positions with a query
-  const int q0 = qb * kQBlock;
+  const int q0 = qb * QB;
   // NS waves share 32 queries, each taking its part (kside) of every key tile
   const int qwave = wave % QG, kside = wave / QG;
   const int qi = q0 + qwave * 32 + col;            // this lane's query position
   const size_t qrow = ((size_t)b * hq + h) * a.T;
-  const int qlast = min(q0 + kQBlock, n) - 1;      // last query of the block inside the prompt
+  const int qlast = min(q0 + QB, n) - 1;      // last query of the block inside the prompt
 
   if (qlast < q0) {  // the whole block lies past the prompt: empty rows
-    for (int e = tid; e < kQBlock * D; e += kThreads) {
+    for (int e = tid; e < QB * D; e += kThreads) {
       const int i = q0 + e / D;
       if (i < a.T) a.out[(qrow + i) * D + e % D] = 0.f;
     }
     if (a.lse)
-      for (int i = q0 + tid; i < min(q0 + kQBlock, a.T); i += kThreads) a.lse[qrow + i] = -INFINITY;
+      for (int i = q0 + tid; i < min(q0 + QB, a.T); i += kThreads) a.lse[qrow + i] = -INFINITY;
     return;
   }
 
@@ -518,7 +524,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
   // lane (col, half) holds dims 32 blk + 8 j + 4 half .. + 3 of query col
   l_run += __shfl_xor(l_run, 32);
-  if (qi < a.T) {
+  if (qi < min(q0 + QB, a.T)) {
     float* op = a.out + (qrow + qi) * D + 4 * half;
     const float inv = (qvalid && l_run > 0.f) ? 1.f / l_run : 0.f;
 #pragma unroll
@@ -534,6 +540,77 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
 }  // namespace
 
+// Queries per block with ns key sides: whole waves of 32, at most 256 / ns, and
+// the prompt divided evenly (128 units of 537 queries in three blocks of 192
+// and not two of 256 and one of 25: 43.3 and 50.9 us).
+static int block_queries(int T, int ns) {
+  const int most = kQueries / ns, n = (T + most - 1) / most;
+  return ((T + n - 1) / n + 31) / 32 * 32;
+}
+
+// Time of a launch of `units` blocks of each of the n costs (descending) on
+// cus CUs, one block at a time each, longest first to the CU that is free
+// first: CUs as groups of equal load, of which each cost splits at most one.
+static float packed_time(const float* cost, int n, long long units, int cus) {
+  struct Group {
+    float load;
+    long long count;
+  };
+  Group g[kPackBlocks + 1];
+  int m = 1;
+  g[0] = {0.f, cus};
+  for (int i = 0; i < n; ++i) {
+    for (long long left = units; left > 0;) {
+      int lo = 0;
+      for (int j = 1; j < m; ++j) lo = g[j].load < g[lo].load ? j : lo;
+      const long long take = std::min(left, g[lo].count);
+      left -= take;
+      if (take == g[lo].count) {
+        g[lo].load += cost[i];
+      } else {
+        g[lo].count -= take;
+        g[m++] = {g[lo].load + cost[i], take};
+      }
+    }
+  }
+  float t = 0.f;
+  for (int j = 0; j < m; ++j) t = std::max(t, g[j].load);
+  return t;
+}
+
+// Key sides of a launch.  One (up to 256 queries a block) is the cheapest per
+// product, but the launch then lasts at least as long as its longest block;
+// two halve that serial length and four quarter it.  The choice is the least
+// time of the blocks packed on the CUs, a block costing `step` for each of
+// its key tiles (64, 128 and 128 keys) and `fixed` once, in us, fitted to 20
+// launches timed with each (within 10%, which a finer split has to gain):
+// 32 heads x 4096 at d 128 187 / 216 / 273 us with one / two / four sides,
+// 128 x 424 26.4 / 35.4 / 43.5, 32 x 2048 84 / 71 / 89, 24 x 2500 113 / 71 /
+// 95, 4 x 8000 279 / 171 / 123, 16 x 1122 42 / 35 / 26, 64 x 200 15.3 / 12.3 /
+// 11.2; at d 64 64 x 505 21.2 / 15.0 / 15.9.
+static int key_sides(int T, int d, long long units, int cus) {
+  if (cus <= 0 || (long long)((T + kQueries - 1) / kQueries) * units >= 8LL * cus) return 1;
+  static const float step[2][3] = {{1.78f, 1.81f, 1.01f}, {2.54f, 2.93f, 1.70f}};
+  static const float fixed[2][3] = {{5.46f, 5.04f, 4.25f}, {4.53f, 6.42f, 7.14f}};
+  int best = 1;
+  float least = INFINITY;
+  for (int i = 0; i < 3; ++i) {
+    const int ns = 1 << i, kt = i == 0 ? 64 : 128, qb = block_queries(T, ns), n = (T + qb - 1) / qb;
+    float cost[kPackBlocks + 1], sum = 0.f, t;
+    for (int j = 0; j < n; ++j) {  // longest first
+      const int keys = std::min((long long)T, (long long)(n - j) * qb);
+      const float c = step[d == 128][i] * (float)((keys + kt - 1) / kt) + fixed[d == 128][i];
+      if (j <= kPackBlocks) cost[j] = c;
+      sum += c;
+    }
+    // many blocks pack evenly
+    t = n > kPackBlocks ? std::max(cost[0], sum * (float)units / (float)cus)
+                        : packed_time(cost, n, units, cus);
+    if (t < least * 0.92f) least = t, best = ns;
+  }
+  return best;
+}
+
 hipError_t launch_prefill(const PrefillLaunch& s, hipStream_t stream) {
   if (s.kv.batch == 0 || s.T == 0) return hipSuccess;
   PrefillArgs a;
@@ -547,23 +624,8 @@ hipError_t launch_prefill(const PrefillLaunch& s, hipStream_t stream) {
   a.out = s.out;
   a.lse = s.lse;
   const long long units = (long long)s.kv.batch * s.kv.hq;
-  const int cus = device_cus();
-  // One key side (256-query blocks) is the cheapest per product, but the
-  // launch then lasts at least as long as its longest block, nqb steps of 256
-  // keys against units * nqb * (nqb + 1) / 2 / CUs steps of work per CU: it is
-  // taken when the latter is at least 11/16 of the former.  Two sides halve
-  // that serial length (128-query blocks), four quarter it.  Measured on 256
-  // CUs, d 128, one / two / four sides, us: 32 heads x 4096 (ratio 1.06)
-  // 187 / 216 / 273, 16 x 6000 (0.78) 225 / 234 / 275, 128 x 424 (0.75)
-  // 26.4 / 35.4 / 43.5, 32 x 2048 (0.56) 84 / 71 / 89, 24 x 2500 (0.52)
-  // 113 / 71 / 95, 4 x 8000 (0.26; two sides 0.5) 279 / 171 / 123,
-  // 16 x 1122 (two sides 0.31) 42 / 35 / 26, 64 x 200 (two sides 0.38)
-  // 15.3 / 12.3 / 11.2.
-  auto fills = [&](int q, int num, int den) {
-    return units * ((s.T + q - 1) / q + 1) * den >= (long long)num * cus;
-  };
-  const int ns = fills(kQueries, 11, 8) ? 1 : fills(kQueries / 2, 5, 4) ? 2 : 4;
-  const int qb = kQueries / ns;
+  const int ns = key_sides(s.T, s.kv.d, units, device_cus());
+  const int qb = a.qblock = block_queries(s.T, ns);
   const dim3 grid((unsigned)(((s.T + qb - 1) / qb) * units));
 #define PRHS_PREFILL_LAUNCH(DV, PG)                                                              \
   do {                                                                                          \
