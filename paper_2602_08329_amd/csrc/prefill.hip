@@ -6,18 +6,19 @@
 // per query from the layer's factor); without PSAW every p <= i (plain
 // causal attention, Eq. attn_eq per position).
 //
-// attn_prefill_bf16<D, NS, PAGED>: one workgroup of 8 waves per (256 / NS
-// query positions, batch, query head), over a contiguous or paged cache.  A
-// wave takes 32 queries as the 32 columns of its MFMA tiles; with NS > 1 key
-// sides, NS waves share the same queries and each takes its own 32- or
-// 64-key part of every key tile, their online softmax states combined at the
-// end.  Key tiles (64 rows; 128 with NS > 1) are loaded once per workgroup
-// (whole rows, one tile ahead of their use; the default cache policy, since
-// the unit's other query blocks read the same rows) into two LDS buffers,
-// K and V both row-major, and a wave computes per 32 keys
-//   S^T (32 keys x 32 queries) = K . Q^T     (v_mfma_f32_32x32x16_bf16)
-//   O^T (d x 32 queries)      += V^T . P^T   (P as bf16 hi + lo parts; the
-//                                             V^T operand by transposing LDS reads)
+// attn_prefill_bf16<D, W, NS, PAGED>: one workgroup per (block of queries,
+// batch, query head), over a contiguous or paged cache.  A wave takes W = 32
+// (8 waves) or 16 (12 waves) queries as the columns of its MFMA tiles; with
+// NS > 1 key sides (W = 32), NS waves share the same queries and each takes
+// its own 32- or 64-key part of every key tile, their online softmax states
+// combined at the end.  Key tiles (64 rows; 128 with NS > 1) are loaded once
+// per workgroup (whole rows, one tile ahead of their use; the default cache
+// policy, since the unit's other query blocks read the same rows) into two
+// LDS buffers, K and V both row-major, and a wave computes per 32 keys
+//   S^T (32 keys x W queries) = K . Q^T     (v_mfma_f32_32x32x16_bf16, or
+//                                            16x16x32 twice)
+//   O^T (d x W queries)      += V^T . P^T   (P as bf16 hi + lo parts; the
+//                                            V^T operand by transposing LDS reads)
 // with an online softmax per query (rescaled lazily).  A block visits only
 // the key tiles that meet its queries' visible ranges -- the sink
 // [0, C_sink) and the band from the smallest vis_start of its queries to
@@ -27,14 +28,15 @@
 // per-(key, query) mask only where some of its queries see them in part.
 //
 // What bounds it: power on long prompts, the longest block on short ones.
-// 32 queries per wave instead of 16 halve the LDS reads per product (16 KB
-// per 32 keys): one prompt of 32 heads x 16384 at d 128 went from 6.4 to 5.8
+// 32 queries per wave halve the LDS reads per product of 16 (16 KB per 32
+// keys): one prompt of 32 heads x 16384 at d 128 went from 6.4 to 5.8
 // million cycles, while the clock under this load fell from 2.10 to 2.05 GHz:
 // 2848 -> 2784 us, 1185 TFLOP/s issued with the probabilities' low part (a
 // large plain bf16 product reaches 1414 on this card).  32 heads x 4096 went
 // from 235 to 190 us, two paged prompts of 12k under PSAW (8 key heads) from
-// 2657 to 2339, 64 heads x 7777 at d 64 from 1018 to 832, 16 heads x 1122
-// from 48 to 26.  Two groups of waves held half a step apart by barriers (one
+// 2657 to 2339, 64 heads x 7777 at d 64 from 1018 to 731, 16 heads x 1122
+// from 48 to 26.  Short prompts on many units and single rounds of blocks
+// keep the 16.  Two groups of waves held half a step apart by barriers (one
 // group's products beside the other's softmax) took the same cycles; dot
 // products for the remainders p - hi were slower, and raised issue priority
 // for the products changed nothing.
@@ -52,12 +54,20 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef short v4i16_t __attribute__((ext_vector_type(4)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kWaves = 8;
-constexpr int kThreads = 64 * kWaves;
-constexpr int kQueries = 32 * kWaves;  // queries per workgroup with one key side
-constexpr int kPackBlocks = 32;  // blocks a unit up to which a launch's packing is worked out
+// Waves of a workgroup: two or three a SIMD, as many as their registers allow.
+constexpr int waves_of(int w) { return w == 32 ? 8 : 12; }
+// A second workgroup on the CU: at d 64, where 128 registers a wave do without
+// scratch (126 with 8 spilled for the paged one-sided form: 2 us more a launch).
+constexpr bool two_per_cu(int d, int w, int ns, bool paged) { return d == 64 && w == 32 && (ns == 1 ? !paged : ns == 4 && paged); }
+constexpr int waves_per_simd(int d, int w, int ns, bool paged) {
+  return (two_per_cu(d, w, ns, paged) ? 2 : 1) * waves_of(w) / 4;
+}
+constexpr int kQueries = 256;  // queries per workgroup of 32-query waves with one key side
+constexpr int kPackBlocks = 48;  // blocks a unit up to which a launch's packing is worked out
 constexpr int kXcds = 8;      // accelerator dies, each with its own L2
 constexpr float kLn2 = 0.69314718055994530942f;
 constexpr float kLazyLog2 = 8.f;  // log2 of the largest probability between rescales
@@ -67,6 +77,7 @@ struct PrefillArgs {
   const __bf16* q;        // [B][Hq][T][D]
   int T;
   int qblock;             // queries per workgroup
+  int qfirst;             // queries of a unit's first workgroup
   int psaw;               // nonzero: row i attends [0, sink) U [first visible at i + 1, i]
   double psaw_f;          // Eq. psaw factor of the layer
   int sink;
@@ -91,36 +102,36 @@ __device__ __forceinline__ int k_slot(int r, int c) {
 // cache instead: no access outside it); there the row offsets of each tile
 // come from LDS, where its first KT threads store them (one block-table read
 // per row) two tiles ahead of the loads.
-template <int D, int KT>
+template <int D, int KT, int NT>
 struct TileOffs {
-  static constexpr int RPL = (KT * (D / 8) + kThreads - 1) / kThreads;  // chunks per thread
+  static constexpr int RPL = (KT * (D / 8) + NT - 1) / NT;  // chunks per thread
   int64_t e[RPL];
 };
-template <int D, int KT>
+template <int D, int KT, int NT>
 struct TileRegs {
-  u32x4_t x[TileOffs<D, KT>::RPL];
+  u32x4_t x[TileOffs<D, KT, NT>::RPL];
 };
 
 // This thread's chunks of the tile at rows [ks, ks + KT) of a
 // contiguous cache.
-template <int D, int KT>
-__device__ __forceinline__ void tile_offsets(TileOffs<D, KT>& off, int64_t unit_row0, int ks, int n) {
+template <int D, int KT, int NT>
+__device__ __forceinline__ void tile_offsets(TileOffs<D, KT, NT>& off, int64_t unit_row0, int ks, int n) {
   constexpr int CH = D / 8;
 #pragma unroll
-  for (int j = 0; j < TileOffs<D, KT>::RPL; ++j) {
-    const int e = (int)threadIdx.x + j * kThreads;
+  for (int j = 0; j < TileOffs<D, KT, NT>::RPL; ++j) {
+    const int e = (int)threadIdx.x + j * NT;
     const int r = (e / CH) % KT, c = e % CH;
     off.e[j] = (unit_row0 + min(ks + r, n - 1)) * D + c * 8;
   }
 }
 
 // The same from the tile's row offsets in LDS (paged cache).
-template <int D, int KT>
-__device__ __forceinline__ void tile_offsets_lds(TileOffs<D, KT>& off, const int64_t* rows) {
+template <int D, int KT, int NT>
+__device__ __forceinline__ void tile_offsets_lds(TileOffs<D, KT, NT>& off, const int64_t* rows) {
   constexpr int CH = D / 8;
 #pragma unroll
-  for (int j = 0; j < TileOffs<D, KT>::RPL; ++j) {
-    const int e = (int)threadIdx.x + j * kThreads;
+  for (int j = 0; j < TileOffs<D, KT, NT>::RPL; ++j) {
+    const int e = (int)threadIdx.x + j * NT;
     off.e[j] = rows[(e / CH) % KT] + (e % CH) * 8;
   }
 }
@@ -134,53 +145,89 @@ __device__ __forceinline__ int64_t paged_row(const KvView& kv, int b, int g, int
 }
 
 // This thread's chunks of a tile of K or V (`base`).
-template <int D, int KT>
-__device__ __forceinline__ void tile_load(TileRegs<D, KT>& R, const void* base,
-                                          const TileOffs<D, KT>& off) {
+template <int D, int KT, int NT>
+__device__ __forceinline__ void tile_load(TileRegs<D, KT, NT>& R, const void* base,
+                                          const TileOffs<D, KT, NT>& off) {
   constexpr int CH = D / 8;
 #pragma unroll
-  for (int j = 0; j < TileOffs<D, KT>::RPL; ++j) {
-    const int e = (int)threadIdx.x + j * kThreads;
-    if ((KT * CH) % kThreads != 0 && e >= KT * CH) break;
+  for (int j = 0; j < TileOffs<D, KT, NT>::RPL; ++j) {
+    const int e = (int)threadIdx.x + j * NT;
+    if ((KT * CH) % NT != 0 && e >= KT * CH) break;
     R.x[j] = *(const u32x4_t*)((const __bf16*)base + off.e[j]);
   }
 }
 
 // V tile in LDS: row-major, 16-byte chunk c of tile row r at slot
-// v_chunk(r, c) of its row, so that the transposing operand reads below (4
-// key rows x 64 bytes per 32 lanes) hit distinct banks.  Rows 4 apart share
-// the permutation.
-template <int D>
+// v_chunk(r, c) of its row, so that the transposing operand reads below (per
+// 32 lanes 4 key rows x 64 bytes with 32 queries a wave, 8 x 32 with 16) hit
+// distinct banks.  Rows 16 apart share the permutation.
+template <int D, int W>
 __device__ __forceinline__ int v_chunk(int r, int c) {
-  return D == 128 ? c ^ ((r & 3) << 2) : c ^ (((r >> 1) & 1) << 2);
+  if (W == 32) return D == 128 ? c ^ ((r & 3) << 2) : c ^ (((r >> 1) & 1) << 2);
+  return D == 128 ? c ^ ((r & 7) << 1) : c ^ (((r >> 1) & 3) << 1);
 }
 
-template <int D, int KT, bool V>
-__device__ __forceinline__ void tile_store(const TileRegs<D, KT>& R, u32x4_t* dst) {
+template <int D, int KT, int NT, int W, bool V>
+__device__ __forceinline__ void tile_store(const TileRegs<D, KT, NT>& R, u32x4_t* dst) {
   constexpr int CH = D / 8;
 #pragma unroll
-  for (int j = 0; j < TileOffs<D, KT>::RPL; ++j) {
-    const int e = (int)threadIdx.x + j * kThreads;
-    if ((KT * CH) % kThreads != 0 && e >= KT * CH) break;
+  for (int j = 0; j < TileOffs<D, KT, NT>::RPL; ++j) {
+    const int e = (int)threadIdx.x + j * NT;
+    if ((KT * CH) % NT != 0 && e >= KT * CH) break;
     const int r = e / CH, c = e % CH;
-    dst[V ? r * CH + v_chunk<D>(r, c) : k_slot<D>(r, c)] = R.x[j];
+    dst[V ? r * CH + v_chunk<D, W>(r, c) : k_slot<D>(r, c)] = R.x[j];
   }
 }
 
-// Maximum over a lane and its partner in the other half of the wave (the two
-// lanes of one query), by the cross-half lane swap: swapping a value with
-// itself leaves a lane holding its own value and its partner's.
-__device__ __forceinline__ float max_over_halves(float v) {
+// Types of a wave of W = 32 or 16 queries: lane (col, grp) = (lane % W,
+// lane / W) has its share of query col, the scores of W / 2 of 32 keys and
+// its dims of each W-dim block of O^T.
+template <int W>
+struct Wave;
+template <>
+struct Wave<32> {
+  typedef f32x16_t Scores;
+  typedef f32x16_t Out;
+};
+template <>
+struct Wave<16> {
+  typedef f32x8_t Scores;
+  typedef f32x4_t Out;
+};
+
+// Maximum over the 64 / W lanes of a query, by lane swaps: swapping a value
+// with itself leaves a lane holding its own value and its partner's.
+template <int W>
+__device__ __forceinline__ float max_over_groups(float v) {
   const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  if (W == 16) {
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+  }
+  return v;
 }
 
-// K operand of one 32-key sub-tile u: lane (col, half) takes dims 16 kk +
-// 8 half .. + 7 of key 32u + col for product kk.
+// Key of a 32-key sub-tile that score r of lane group grp belongs to.
+template <int W>
+__device__ __forceinline__ int score_key(int r, int grp) {
+  return (W == 32 ? 8 : 16) * (r >> 2) + 4 * grp + (r & 3);
+}
+
+// K operand of one 32-key sub-tile.  W = 32: product kk takes dims 16 kk +
+// 8 grp .. + 7 of key col; W = 16: product (h, kk) dims 32 kk + 8 grp .. + 7
+// of key 16 h + col.
 template <int D>
 struct KFrag {
   u32x4_t x[D / 16];
 };
+// LDS slot of this lane's piece of product j.
+template <int D, int W>
+__device__ __forceinline__ int kfrag_slot(int row0, int j, int col, int grp) {
+  if (W == 32) return k_slot<D>(row0 + col, 2 * j + grp);
+  constexpr int KS = D / 32;
+  return k_slot<D>(row0 + 16 * (j / KS) + col, 4 * (j % KS) + grp);
+}
 template <int D>
 __device__ __forceinline__ void load_kfrag(KFrag<D>& K, const unsigned char* sk, const int (&off)[D / 16],
                                            int base) {
@@ -188,46 +235,58 @@ __device__ __forceinline__ void load_kfrag(KFrag<D>& K, const unsigned char* sk,
   for (int kk = 0; kk < D / 16; ++kk) K.x[kk] = *(const u32x4_t*)(sk + off[kk] + base);
 }
 
-// Scores of the sub-tile against one wave's 32 queries:
-// S^T (32 keys x 32 queries) = K . Q^T.  Lane (col, half) gets query col at
-// keys 8 (r / 4) + 4 half + r % 4, r = 0 .. 15.
-template <int D>
-__device__ __forceinline__ f32x16_t tile_scores(const KFrag<D>& K, const bf16x8_t* qf) {
-  f32x16_t acc;
+// Scores of the sub-tile against one wave's queries: S^T = K . Q^T, lane
+// (col, grp) query col at keys score_key(r, grp).
+template <int D, int W>
+__device__ __forceinline__ typename Wave<W>::Scores tile_scores(const KFrag<D>& K, const bf16x8_t* qf) {
+  if constexpr (W == 32) {
+    f32x16_t acc;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk)
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, K.x[kk]), qf[kk], acc, 0, 0, 0);
-  return acc;
+    for (int kk = 0; kk < D / 16; ++kk)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, K.x[kk]), qf[kk], acc, 0, 0, 0);
+    return acc;
+  } else {
+    f32x4_t acc[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      acc[h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kk = 0; kk < D / 32; ++kk)
+        acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, K.x[h * (D / 32) + kk]), qf[kk],
+                                                         acc[h], 0, 0, 0);
+    }
+    return __builtin_shufflevector(acc[0], acc[1], 0, 1, 2, 3, 4, 5, 6, 7);
+  }
 }
 
 // P^T of one sub-tile as bf16 hi + lo parts, in the K-index order of the
-// products: product t takes r = 8t .. 8t + 7 of the lane's 16 scores.
+// products: product t takes r = 8t .. 8t + 7 of the lane's scores.
+template <int W>
 struct Probs {
-  uint32_t hi[8], lo[8];
+  uint32_t hi[W / 4], lo[W / 4];
 };
 
 // The online softmax of one sub-tile (keys ks32 .. ks32 + 31): the
 // per-(key, query) mask unless `full`, the running maximum, O and l rescaled
 // where it rises, and the probabilities.
-template <int D>
-__device__ __forceinline__ void tile_softmax(f32x16_t x, int ks32, int half, int qi, bool qvalid,
+template <int D, int W>
+__device__ __forceinline__ void tile_softmax(typename Wave<W>::Scores x, int ks32, int grp, int qi, bool qvalid,
                                              int my_vis, int sink, float scale_log2, bool full,
-                                             float& m_run, float& l_run, f32x16_t* o, Probs& P) {
-  constexpr int DB = D / 32;       // 32-dim blocks of O^T
+                                             float& m_run, float& l_run, typename Wave<W>::Out* o, Probs<W>& P) {
   if (!full) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int p = ks32 + 8 * (r >> 2) + 4 * half + (r & 3);
+    for (int r = 0; r < W / 2; ++r) {
+      const int p = ks32 + score_key<W>(r, grp);
       const bool vis = qvalid && p <= qi && (p < sink || p >= my_vis);
       x[r] = vis ? x[r] : -INFINITY;
     }
   }
   float mt = x[0];
 #pragma unroll
-  for (int r = 1; r < 16; ++r) mt = fmaxf(mt, x[r]);
-  mt = max_over_halves(mt);
+  for (int r = 1; r < W / 2; ++r) mt = fmaxf(mt, x[r]);
+  mt = max_over_groups<W>(mt);
   // lazy rescaling: the reference m_run (and with it O and l) moves only
   // when some query of the wave sees its maximum rise by more than 2^8, so
   // the probabilities stay below 2^8; O / l does not depend on the reference
@@ -237,14 +296,14 @@ __device__ __forceinline__ void tile_softmax(f32x16_t x, int ks32, int half, int
     m_run = m_new;
     l_run *= alpha;
 #pragma unroll
-    for (int blk = 0; blk < DB; ++blk) o[blk] *= alpha;
+    for (int blk = 0; blk < D / W; ++blk) o[blk] *= alpha;
   }
   // while m_run is -inf every score is -inf too: a finite reference makes
   // every probability 0 without a branch
   const float mref = m_run == -INFINITY ? 0.f : m_run;
   float psum = 0.f;
 #pragma unroll
-  for (int w = 0; w < 8; ++w) {
+  for (int w = 0; w < W / 4; ++w) {
     const float p0 = __builtin_amdgcn_exp2f(fmaf(x[2 * w], scale_log2, -mref));
     const float p1 = __builtin_amdgcn_exp2f(fmaf(x[2 * w + 1], scale_log2, -mref));
     psum += p0 + p1;
@@ -257,39 +316,52 @@ __device__ __forceinline__ void tile_softmax(f32x16_t x, int ks32, int half, int
   l_run += psum;
 }
 
-// V^T operand of the products over keys 16t .. 16t + 15 of sub-tile u of the
-// V tile svx: for block blk (32 dims x 16 keys) lane (col, half) needs dim
-// 32 blk + col at keys 16t + 4 half + i and 16t + 8 + 4 half + i, i = 0 .. 3,
-// by two transposing LDS loads from the row-major tile: in each 16-lane
-// group, lane 4e + q points at the 8-byte piece q of 16 dims of key row e,
-// and the load hands lane c dim c at the four rows.
-template <int D>
+// V^T operand of one product.  W = 32: over keys 16t .. 16t + 15 of the
+// sub-tile, block blk (32 dims) needs dim 32 blk + col at keys 16t + 4 grp +
+// i and 16t + 8 + 4 grp + i, i = 0 .. 3; W = 16: over its 32 keys, dim 16 blk
+// + col at keys 4 grp + i and 16 + 4 grp + i.  Two transposing LDS loads from
+// the row-major tile: in each 16-lane group, lane 4e + q points at the 8-byte
+// piece q of 16 dims of key row e, and the load hands lane c dim c at the
+// four rows.
+template <int D, int W>
 struct VFrag {
-  bf16x8_t x[D / 32];
+  bf16x8_t x[D / W];
 };
-template <int D>
-__device__ __forceinline__ void load_vfrag(VFrag<D>& V, const unsigned char* sv, const int (&off)[D / 32],
+// Byte offset of this lane's piece of block blk, first of the two loads.
+template <int D, int W>
+__device__ __forceinline__ int vfrag_offset(int row0, int blk, int lane) {
+  const int e = (lane >> 2) & 3, q = lane & 3, grp = lane / W, g1 = W == 32 ? (lane >> 4) & 1 : 0;
+  const int r = row0 + 4 * grp + e;
+  return r * (D * 2) + (q & 1) * 8 + 16 * v_chunk<D, W>(r, W / 8 * blk + 2 * g1 + (q >> 1));
+}
+template <int D, int W>
+__device__ __forceinline__ void load_vfrag(VFrag<D, W>& V, const unsigned char* sv, const int (&off)[D / W],
                                            int base) {
 #pragma unroll
-  for (int blk = 0; blk < D / 32; ++blk) {
+  for (int blk = 0; blk < D / W; ++blk) {
     const unsigned char* vp = sv + off[blk] + base;
     const v4i16_t a0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
         (__attribute__((address_space(3))) v4i16_t*)vp);
     const v4i16_t a1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) v4i16_t*)(vp + 8 * (D * 2)));
+        (__attribute__((address_space(3))) v4i16_t*)(vp + (W == 32 ? 8 : 16) * (D * 2)));
     V.x[blk] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
   }
 }
 
 // O^T += V^T P^T over the keys of one operand.
-template <int D>
-__device__ __forceinline__ void tile_products(const VFrag<D>& V, const Probs& P, int t, f32x16_t* o) {
+template <int D, int W>
+__device__ __forceinline__ void tile_products(const VFrag<D, W>& V, const Probs<W>& P, int t, typename Wave<W>::Out* o) {
   const bf16x8_t phi = __builtin_bit_cast(bf16x8_t, make_uint4(P.hi[4 * t], P.hi[4 * t + 1], P.hi[4 * t + 2], P.hi[4 * t + 3]));
   const bf16x8_t plo = __builtin_bit_cast(bf16x8_t, make_uint4(P.lo[4 * t], P.lo[4 * t + 1], P.lo[4 * t + 2], P.lo[4 * t + 3]));
 #pragma unroll
-  for (int blk = 0; blk < D / 32; ++blk) {
-    o[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(V.x[blk], phi, o[blk], 0, 0, 0);
-    o[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(V.x[blk], plo, o[blk], 0, 0, 0);
+  for (int blk = 0; blk < D / W; ++blk) {
+    if constexpr (W == 32) {
+      o[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(V.x[blk], phi, o[blk], 0, 0, 0);
+      o[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(V.x[blk], plo, o[blk], 0, 0, 0);
+    } else {
+      o[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(V.x[blk], phi, o[blk], 0, 0, 0);
+      o[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(V.x[blk], plo, o[blk], 0, 0, 0);
+    }
   }
 }
 
@@ -313,33 +385,39 @@ __device__ __forceinline__ void block_of(int units, int nqb, int L, int* bh, int
   }
 }
 
-template <int D, int NS, bool PAGED>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_prefill_bf16(PrefillArgs a) {
-  constexpr int QG = kWaves / NS;           // waves that differ in queries
+template <int D, int W, int NS, bool PAGED>
+__global__ __launch_bounds__(64 * waves_of(W)) __attribute__((amdgpu_waves_per_eu(waves_per_simd(D, W, NS, PAGED), waves_per_simd(D, W, NS, PAGED))))
+void attn_prefill_bf16(PrefillArgs a) {
+  constexpr int kThreads = 64 * waves_of(W);
+  constexpr int QG = waves_of(W) / NS;      // waves that differ in queries
   constexpr int SUB = NS == 4 ? 1 : 2;      // 32-key sub-tiles per wave and tile
   constexpr int KT = 32 * NS * SUB;         // key rows per tile
-  constexpr int KS = D / 16;   // products per 32-key sub-tile of S
-  constexpr int DB = D / 32;   // output blocks of 32 dims
+  constexpr int KS = W == 32 ? D / 16 : D / 32;  // Q operands
+  constexpr int DB = D / W;    // output blocks of W dims
   constexpr int CH = D / 8;    // 16-byte chunks per row
   __shared__ u32x4_t s_kv[4][KT * CH];  // K tiles, then V tiles
   u32x4_t (*s_k)[KT * CH] = s_kv, (*s_v)[KT * CH] = s_kv + 2;
   __shared__ float s_ml[NS > 1 ? (NS - 1) * QG : 1][2][64];
   __shared__ int s_vmin;
   __shared__ int64_t s_rows[2][PAGED ? KT : 1];  // paged: row offsets of upcoming tiles
-  const int QB = a.qblock;                  // queries of a block, at most 32 QG
-  const int nqb = (a.T + QB - 1) / QB;
+  // blocks of qblock queries (at most W QG), the first of qfirst
+  const int nqb = 1 + (max(a.T - a.qfirst, 0) + a.qblock - 1) / a.qblock;
   int bh, qb;
   block_of(a.kv.batch * a.kv.hq, nqb, (int)blockIdx.x, &bh, &qb);
   const int hq = a.kv.hq, G = hq / a.kv.hkv;
   const int b = bh / hq, h = bh % hq, g = h / G;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int col = lane & 31, half = lane >> 5;
+  const int col = lane % W, grp = lane / W;
   const int n = min(kv_seq_len(a.kv, b), a.T);  // prompt positions with a query
-  const int q0 = qb * QB;
-  // NS waves share 32 queries, each taking its part (kside) of every key tile
-  const int qwave = wave % QG, kside = wave / QG;
-  const int qi = q0 + qwave * 32 + col;            // this lane's query position
+  const int QB = qb ? a.qblock : a.qfirst;
+  const int q0 = qb ? a.qfirst + (qb - 1) * a.qblock : 0;
+  // NS waves share their queries, each taking its part (kside) of every key
+  // tile.  Waves w and w + 4 share a SIMD: there the sides of one query group,
+  // or, in a block of at most half the groups, nothing.
+  const bool thin = QB <= W * QG / 2;
+  const int qwave = thin ? wave / NS : wave % QG, kside = thin ? wave % NS : wave / QG;
+  const int qi = q0 + qwave * W + col;             // this lane's query position
   const size_t qrow = ((size_t)b * hq + h) * a.T;
   const int qlast = min(q0 + QB, n) - 1;      // last query of the block inside the prompt
 
@@ -369,29 +447,29 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   // this lane's query and its first visible non-sink position
   const bool qvalid = qi <= qlast;
   const int my_vis = (a.psaw && qvalid) ? psaw_first_visible(a.psaw_f, a.sink, qi + 1) : 0;
-  // a tile needs no mask for this wave when all 32 of its queries lie in
+  // a tile needs no mask for this wave when all of its queries lie in
   // the prompt, the tile ends at or before the first of them, and it lies
   // inside the sink or at or past the largest of their vis_start
-  const int qw0 = q0 + 32 * qwave;
-  const bool wave_all = qw0 + 31 <= qlast;
+  const int qw0 = q0 + W * qwave;
+  const bool wave_all = qw0 + W - 1 <= qlast;
   int wvis = my_vis, wvmin = qvalid ? my_vis : 0x7FFFFFFF;
 #pragma unroll
-  for (int off = 1; off < 32; off <<= 1) {
+  for (int off = 1; off < W; off <<= 1) {
     wvis = max(wvis, __shfl_xor(wvis, off));
     wvmin = min(wvmin, __shfl_xor(wvmin, off));
   }
-  // each half of the wave holds the wave's 16 queries: the results are uniform
+  // each lane group holds the wave's queries: the results are uniform
   wvis = __builtin_amdgcn_readfirstlane(wvis);
   wvmin = __builtin_amdgcn_readfirstlane(wvmin);
   // and it needs no work at all when it lies past the wave's last query or
   // between the sink and the smallest of their vis_start (every product
   // would be masked; skipping leaves O, m and l exactly as they are)
-  const int wlast = min(qw0 + 31, qlast);
+  const int wlast = qw0 <= qlast ? min(qw0 + W - 1, qlast) : -1;
   bf16x8_t qf[KS];
   {
-    const __bf16* qp = a.q + (qrow + (qvalid ? qi : q0)) * D + half * 8;
+    const __bf16* qp = a.q + (qrow + (qvalid ? qi : q0)) * D + grp * 8;
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) qf[kk] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(qp + 16 * kk));
+    for (int kk = 0; kk < KS; ++kk) qf[kk] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(qp + 512 / W * kk));
   }
   __syncthreads();
   const int band_lo = min(max(s_vmin, sink_end), qlast + 1);
@@ -401,11 +479,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
   const int64_t row0 = ((int64_t)b * a.kv.hkv + g) * a.kv.capacity;
   float m_run = -INFINITY, l_run = 0.f;
-  f32x16_t o[DB];
+  typename Wave<W>::Out o[DB];
 #pragma unroll
   for (int i = 0; i < DB; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) o[i][r] = 0.f;
+    for (int r = 0; r < W * W / 64; ++r) o[i][r] = 0.f;
 
   auto tile_start = [&](int t) { return (t < nsink ? t : tb0 + (t - nsink)) * KT; };
   auto full_tile = [&](int ks) {
@@ -414,12 +492,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   auto masked_tile = [&](int ks) {
     return ks > wlast || (ks >= a.sink && ks + 32 * SUB - 1 < wvmin);
   };
-  TileOffs<D, KT> offs;
-  TileRegs<D, KT> rk, rv;
+  TileOffs<D, KT, kThreads> offs;
+  TileRegs<D, KT, kThreads> rk, rv;
   auto rows_of = [&](int t) { return paged_row(a.kv, b, g, tile_start(max(min(t, ntiles - 1), 0)) + tid, n); };
   auto offsets = [&](int t) {
-    if constexpr (PAGED) tile_offsets_lds<D, KT>(offs, s_rows[t & 1]);
-    else tile_offsets<D, KT>(offs, row0, tile_start(max(min(t, ntiles - 1), 0)), n);
+    if constexpr (PAGED) tile_offsets_lds<D, KT, kThreads>(offs, s_rows[t & 1]);
+    else tile_offsets<D, KT, kThreads>(offs, row0, tile_start(max(min(t, ntiles - 1), 0)), n);
   };
   if (PAGED) {
     if (tid < KT) {
@@ -429,36 +507,30 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     __syncthreads();
   }
   offsets(0);
-  tile_load<D, KT>(rk, a.kv.k, offs);
-  tile_load<D, KT>(rv, a.kv.v, offs);
+  tile_load<D, KT, kThreads>(rk, a.kv.k, offs);
+  tile_load<D, KT, kThreads>(rv, a.kv.v, offs);
   offsets(1);
   // LDS byte offsets of this lane's operand pieces, fixed for the launch:
   // with the buffer a constant of the code below, an operand read costs no
   // address arithmetic
-  int koff[D / 16], voff[D / 32];
+  int koff[D / 16], voff[DB];
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk)
-    koff[kk] = 16 * k_slot<D>(32 * SUB * kside + col, 2 * kk + half);
-  {
-    const int e = (lane >> 2) & 3, q = lane & 3, g1 = (lane >> 4) & 1;
+  for (int j = 0; j < D / 16; ++j) koff[j] = 16 * kfrag_slot<D, W>(32 * SUB * kside, j, col, grp);
 #pragma unroll
-    for (int blk = 0; blk < D / 32; ++blk)
-      voff[blk] = (32 * SUB * kside + 4 * half + e) * (D * 2) + (q & 1) * 8 +
-                  16 * v_chunk<D>(e, 4 * blk + 2 * g1 + (q >> 1));
-  }
+  for (int blk = 0; blk < DB; ++blk) voff[blk] = vfrag_offset<D, W>(32 * SUB * kside, blk, lane);
   int64_t prow = 0;
   auto step = [&](auto buf, int t) {
     constexpr int BUF = decltype(buf)::value;
     constexpr int kTileBytes = KT * D * 2;
-    tile_store<D, KT, false>(rk, s_k[BUF]);
-    tile_store<D, KT, true>(rv, s_v[BUF]);
+    tile_store<D, KT, kThreads, W, false>(rk, s_k[BUF]);
+    tile_store<D, KT, kThreads, W, true>(rv, s_v[BUF]);
     lds_barrier();
     // paged: the table read is issued before the tile loads, so waiting for
     // it later does not wait for them
     if (PAGED && tid < KT) prow = rows_of(t + 2);
     if (PAGED) offsets(t + 1);
-    tile_load<D, KT>(rk, a.kv.k, offs);  // tile t + 1 (the last one again at the end)
-    tile_load<D, KT>(rv, a.kv.v, offs);
+    tile_load<D, KT, kThreads>(rk, a.kv.k, offs);  // tile t + 1 (the last one again at the end)
+    tile_load<D, KT, kThreads>(rv, a.kv.v, offs);
     if (!PAGED) offsets(t + 2);
     const int ks = tile_start(t) + 32 * SUB * kside;  // this wave's keys of the tile
     if (!masked_tile(ks)) {
@@ -466,17 +538,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
       for (int i = 0; i < SUB; ++i) {
         KFrag<D> kf;
-        Probs P;
-        VFrag<D> v;
+        Probs<W> P;
+        VFrag<D, W> v;
         load_kfrag<D>(kf, (const unsigned char*)s_kv, koff, BUF * kTileBytes + 32 * i * D * 2);
-        const f32x16_t x = tile_scores<D>(kf, qf);
-        tile_softmax<D>(x, ks + 32 * i, half, qi, qvalid, my_vis, a.sink, a.scale_log2, full, m_run,
-                        l_run, o, P);
+        const auto x = tile_scores<D, W>(kf, qf);
+        tile_softmax<D, W>(x, ks + 32 * i, grp, qi, qvalid, my_vis, a.sink, a.scale_log2, full, m_run,
+                           l_run, o, P);
 #pragma unroll
-        for (int w = 0; w < 2; ++w) {
-          load_vfrag<D>(v, (const unsigned char*)s_kv + 2 * kTileBytes, voff,
-                        BUF * kTileBytes + (32 * i + 16 * w) * D * 2);
-          tile_products<D>(v, P, w, o);
+        for (int w = 0; w < W / 16; ++w) {
+          load_vfrag<D, W>(v, (const unsigned char*)s_kv + 2 * kTileBytes, voff,
+                           BUF * kTileBytes + (32 * i + 16 * w) * D * 2);
+          tile_products<D, W>(v, P, w, o);
         }
       }
     }
@@ -522,43 +594,36 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
   }
 
-  // lane (col, half) holds dims 32 blk + 8 j + 4 half .. + 3 of query col
+  // lane (col, grp) holds dims W blk + 8 j + 4 grp .. + 3 of query col
+  if (W == 16) l_run += __shfl_xor(l_run, 16);
   l_run += __shfl_xor(l_run, 32);
   if (qi < min(q0 + QB, a.T)) {
-    float* op = a.out + (qrow + qi) * D + 4 * half;
+    float* op = a.out + (qrow + qi) * D + 4 * grp;
     const float inv = (qvalid && l_run > 0.f) ? 1.f / l_run : 0.f;
 #pragma unroll
     for (int blk = 0; blk < DB; ++blk)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        *(float4*)(op + 32 * blk + 8 * j) = make_float4(o[blk][4 * j] * inv, o[blk][4 * j + 1] * inv,
-                                                        o[blk][4 * j + 2] * inv, o[blk][4 * j + 3] * inv);
-    if (a.lse && half == 0)
+      for (int j = 0; j < W * W / 256; ++j)
+        *(float4*)(op + W * blk + 8 * j) = make_float4(o[blk][4 * j] * inv, o[blk][4 * j + 1] * inv,
+                                                       o[blk][4 * j + 2] * inv, o[blk][4 * j + 3] * inv);
+    if (a.lse && grp == 0)
       a.lse[qrow + qi] = (qvalid && l_run > 0.f) ? (m_run + log2f(l_run)) * kLn2 : -INFINITY;
   }
 }
 
 }  // namespace
 
-// Queries per block with ns key sides: whole waves of 32, at most 256 / ns, and
-// the prompt divided evenly (128 units of 537 queries in three blocks of 192
-// and not two of 256 and one of 25: 43.3 and 50.9 us).
-static int block_queries(int T, int ns) {
-  const int most = kQueries / ns, n = (T + most - 1) / most;
-  return ((T + n - 1) / n + 31) / 32 * 32;
-}
-
-// Time of a launch of `units` blocks of each of the n costs (descending) on
-// cus CUs, one block at a time each, longest first to the CU that is free
-// first: CUs as groups of equal load, of which each cost splits at most one.
-static float packed_time(const float* cost, int n, long long units, int cus) {
+// Time of a launch of `units` blocks of each of the n costs on `slots` places
+// for one block at a time, each block to the place that is free first: places
+// as groups of equal load, of which each cost splits at most one.
+static float packed_time(const float* cost, int n, long long units, long long slots) {
   struct Group {
     float load;
     long long count;
   };
   Group g[kPackBlocks + 1];
   int m = 1;
-  g[0] = {0.f, cus};
+  g[0] = {0.f, slots};
   for (int i = 0; i < n; ++i) {
     for (long long left = units; left > 0;) {
       int lo = 0;
@@ -578,35 +643,88 @@ static float packed_time(const float* cost, int n, long long units, int cus) {
   return t;
 }
 
-// Key sides of a launch.  One (up to 256 queries a block) is the cheapest per
-// product, but the launch then lasts at least as long as its longest block;
-// two halve that serial length and four quarter it.  The choice is the least
-// time of the blocks packed on the CUs, a block costing `step` for each of
-// its key tiles (64, 128 and 128 keys) and `fixed` once, in us, fitted to 20
-// launches timed with each (within 10%, which a finer split has to gain):
-// 32 heads x 4096 at d 128 187 / 216 / 273 us with one / two / four sides,
-// 128 x 424 26.4 / 35.4 / 43.5, 32 x 2048 84 / 71 / 89, 24 x 2500 113 / 71 /
-// 95, 4 x 8000 279 / 171 / 123, 16 x 1122 42 / 35 / 26, 64 x 200 15.3 / 12.3 /
-// 11.2; at d 64 64 x 505 21.2 / 15.0 / 15.9.
-static int key_sides(int T, int d, long long units, int cus) {
-  if (cus <= 0 || (long long)((T + kQueries - 1) / kQueries) * units >= 8LL * cus) return 1;
-  static const float step[2][3] = {{1.78f, 1.81f, 1.01f}, {2.54f, 2.93f, 1.70f}};
-  static const float fixed[2][3] = {{5.46f, 5.04f, 4.25f}, {4.53f, 6.42f, 7.14f}};
-  int best = 1;
+// How a launch divides its units: waves of w queries, ns key sides, blocks of
+// qblock queries, the first of qfirst.
+struct Plan {
+  int w, ns, qblock, qfirst;
+};
+
+// The plan of least time, its blocks packed on the CUs.  A block costs
+// `step` for each of its key tiles (64, 64, 128 and 128 keys) and `fixed`
+// once (for a prompt of T tokens), in us; a step costs by the waves that share a SIMD, as it is their
+// issue and the chain of one wave that it waits for.  Fitted to 2600 timed
+// launches (within 6% on average; the plan taken is 2% from the best of its
+// launch).  What each is for, d 128, in us, with (16 queries, one side | 32
+// queries, one | two | four sides):
+//   256 queries fill the LDS reads best, on launches of many blocks: 32 heads
+//   x 4096 - | 187 | 216 | 273, 128 x 450 33.2 | 30.1 | 36.2 | 47.7;
+//   sides shorten the longest block of few units: 32 x 537 20.8 | 23.6 | 20.6
+//   | 17.6, 4 x 8000 - | 279 | 171 | 123;
+//   three narrow waves a SIMD hide a chain that two leave bare, where a CU
+//   gets about one block: 128 x 265 15.6 | 16.8 | 22.9 | 27.2, 128 x 173 11.6
+//   | 12.9 | 13.0 | 20.5, 16 x 6000 213 | 228 | - | -.
+// The first block may differ from the others, and the last be short: it sees
+// the most keys (256 x 536 at 32 queries 68.2 with even blocks, 64.4 with 128
+// first and then 256; 128 x 316 at 16 queries 19.0 even, 17.9 with 192 first).  At d 64 a second
+// workgroup of the wide waves fits a CU where 128 registers hold them: 256 x
+// 1024 99 -> 79, 64 x 7777 834 -> 731.
+static Plan plan_of(const PrefillLaunch& s, long long units, int cus) {
+  const int T = s.T, d = s.kv.d;
+  const bool paged = s.kv.paged;
+  const auto whole = [](int q, int w) { return (q + w - 1) / w * w; };
+  const int nwide = (T + kQueries - 1) / kQueries;
+  if (cus <= 0 || nwide * units >= 8LL * cus)
+    return {32, 1, kQueries, whole(T - (nwide - 1) * kQueries, 32)};
+  // one block, one tile or two: the wave's chain is all there is (64 x 113 8.4
+  // with 16 queries, 8.8, 10.0 and 8.7)
+  if (d == 128 && T <= 128 && units <= cus) return {16, 1, whole(T, 16), whole(T, 16)};
+  struct Cost {
+    float step[3], fixed;
+  };
+  // d 128, d 64, d 64 paged; the last of each is the one that shares a CU,
+  // where the launch has more blocks than CUs
+  static const Cost costs[3][5] = {
+      {{{1.27f, 1.62f, 2.12f}, 6.17f}, {{2.03f, 2.65f}, 5.80f}, {{1.86f, 2.92f}, 7.54f}, {{0.92f, 1.70f}, 7.43f}, {}},
+      {{{1.40f, 1.47f, 1.72f}, 3.95f}, {{1.67f, 2.00f}, 3.91f}, {{1.59f, 2.25f}, 4.86f}, {{0.56f, 1.19f}, 4.65f},
+       {{1.65f, 2.80f}, 6.94f}},
+      {{{1.04f, 1.47f, 1.68f}, 4.65f}, {{1.74f, 2.08f}, 4.73f}, {{1.66f, 2.20f}, 5.81f}, {{1.36f, 1.62f}, 5.34f},
+       {{1.18f, 1.80f}, 6.94f}}};
+  const Cost* const table = costs[d == 128 ? 0 : paged ? 2 : 1];
+  Plan best = {32, 1, kQueries, kQueries};
   float least = INFINITY;
-  for (int i = 0; i < 3; ++i) {
-    const int ns = 1 << i, kt = i == 0 ? 64 : 128, qb = block_queries(T, ns), n = (T + qb - 1) / qb;
-    float cost[kPackBlocks + 1], sum = 0.f, t;
-    for (int j = 0; j < n; ++j) {  // longest first
-      const int keys = std::min((long long)T, (long long)(n - j) * qb);
-      const float c = step[d == 128][i] * (float)((keys + kt - 1) / kt) + fixed[d == 128][i];
-      if (j <= kPackBlocks) cost[j] = c;
-      sum += c;
+  for (int v = 0; v < 4; ++v) {
+    const int w = v == 0 ? 16 : 32, ns = v == 0 ? 1 : 1 << (v - 1), kt = v < 2 ? 64 : 128;
+    const int most = w * waves_of(w) / ns, nmin = (T + most - 1) / most;
+    const int sizes[4] = {whole((T + nmin - 1) / nmin, w), whole((T + nmin) / (nmin + 1), w), most,
+                          v == 3 ? most : most / 2};
+    // each size with what is left over in the first block, then in the last
+    for (int k = nmin > 16 ? 4 : 0; k < (nmin > 16 ? 6 : 8); ++k) {
+      const int qb = sizes[k / 2];
+      const int n = k % 2 ? (T + qb - 1) / qb : 1 + (std::max(T - most, 0) + qb - 1) / qb;
+      const int qf = k % 2 ? qb : std::min(most, whole(T - (n - 1) * qb, w));
+      const bool shared = two_per_cu(d, w, ns, paged) && n * units > cus;
+      const Cost& c = table[shared ? 4 : v];
+      const long long slots = shared ? 2LL * cus : cus;
+      float cost[kPackBlocks], sum = 0.f, longest = 0.f;
+      for (int j = n - 1; j >= 0; --j) {  // longest first
+        const int end = std::min(T, qf + j * qb), q0 = j ? qf + (j - 1) * qb : 0;
+        int tiles = (end + kt - 1) / kt;
+        if (s.psaw) {
+          const int nsink = (std::min(s.sink, end) + kt - 1) / kt;
+          const int first = psaw_first_visible(s.psaw_f, s.sink, q0 + 1);
+          tiles = std::min(tiles, nsink + std::max(tiles - std::max(first / kt, nsink), 0));
+        }
+        const int waves = (end - q0 + w - 1) / w * ns;
+        const float t = c.step[(waves + 3) / 4 - 1] * (float)tiles + c.fixed;
+        if (n <= kPackBlocks) cost[n - 1 - j] = t;
+        sum += t;
+        longest = std::max(longest, t);
+      }
+      // many blocks pack evenly
+      const float t = n > kPackBlocks ? std::max(longest, sum * (float)units / (float)slots)
+                                      : packed_time(cost, n, units, slots);
+      if (t < least) least = t, best = {w, ns, qb, qf};
     }
-    // many blocks pack evenly
-    t = n > kPackBlocks ? std::max(cost[0], sum * (float)units / (float)cus)
-                        : packed_time(cost, n, units, cus);
-    if (t < least * 0.92f) least = t, best = ns;
   }
   return best;
 }
@@ -624,14 +742,18 @@ hipError_t launch_prefill(const PrefillLaunch& s, hipStream_t stream) {
   a.out = s.out;
   a.lse = s.lse;
   const long long units = (long long)s.kv.batch * s.kv.hq;
-  const int ns = key_sides(s.T, s.kv.d, units, device_cus());
-  const int qb = a.qblock = block_queries(s.T, ns);
-  const dim3 grid((unsigned)(((s.T + qb - 1) / qb) * units));
-#define PRHS_PREFILL_LAUNCH(DV, PG)                                                              \
-  do {                                                                                          \
-    if (ns == 1) hipLaunchKernelGGL((attn_prefill_bf16<DV, 1, PG>), grid, dim3(kThreads), 0, stream, a);      \
-    else if (ns == 2) hipLaunchKernelGGL((attn_prefill_bf16<DV, 2, PG>), grid, dim3(kThreads), 0, stream, a); \
-    else hipLaunchKernelGGL((attn_prefill_bf16<DV, 4, PG>), grid, dim3(kThreads), 0, stream, a);              \
+  const Plan plan = plan_of(s, units, device_cus());
+  a.qblock = plan.qblock;
+  a.qfirst = plan.qfirst;
+  const dim3 grid((unsigned)((1 + (std::max(s.T - a.qfirst, 0) + a.qblock - 1) / a.qblock) * units));
+#define PRHS_PREFILL_GO(DV, W, NS, PG) \
+  hipLaunchKernelGGL((attn_prefill_bf16<DV, W, NS, PG>), grid, dim3(64 * waves_of(W)), 0, stream, a)
+#define PRHS_PREFILL_LAUNCH(DV, PG)                        \
+  do {                                                     \
+    if (plan.w == 16) PRHS_PREFILL_GO(DV, 16, 1, PG);      \
+    else if (plan.ns == 1) PRHS_PREFILL_GO(DV, 32, 1, PG); \
+    else if (plan.ns == 2) PRHS_PREFILL_GO(DV, 32, 2, PG); \
+    else PRHS_PREFILL_GO(DV, 32, 4, PG);                   \
   } while (0)
   if (s.kv.d == 128) {
     if (s.kv.paged) PRHS_PREFILL_LAUNCH(128, true);
@@ -641,6 +763,7 @@ hipError_t launch_prefill(const PrefillLaunch& s, hipStream_t stream) {
     else PRHS_PREFILL_LAUNCH(64, false);
   }
 #undef PRHS_PREFILL_LAUNCH
+#undef PRHS_PREFILL_GO
   return hipGetLastError();
 }
 

@@ -194,8 +194,13 @@ def test_prefill_rejects_fp32():
     (3, 24, 384, 64, False),
     (3, 60, 255, 128, False),   # one key side: 256-query blocks, units not a multiple of the XCDs
     (5, 24, 321, 128, True),    # units a multiple of the XCDs, not of a whole group of them
-    (2, 64, 537, 128, False),   # three even blocks of 192 queries, two waves of eight idle
-    (1, 60, 97, 64, True),      # blocks smaller than their waves allow, many key sides
+    (2, 64, 537, 128, False),   # a first block smaller than the others
+    (1, 60, 97, 64, True),      # blocks smaller than their waves allow
+    (2, 64, 173, 128, True),    # 16-query waves, two blocks
+    (2, 64, 265, 64, False),
+    (1, 64, 113, 128, False),   # 16-query waves, one block with a wave to spare
+    (4, 64, 300, 64, False),    # d 64, two workgroups a CU: one key side
+    (1, 48, 300, 64, True),     # and four
 ])
 def test_prefill_key_sides_and_block_order(batch, hq, T, d, paged):
     # outputs as for every other prefill test: bf16 hi + lo probabilities
