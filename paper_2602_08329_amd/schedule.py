@@ -18,6 +18,7 @@ lengths n0, which are simply the sequence lengths of the refresh step.
 
 from __future__ import annotations
 
+import functools
 import math
 
 import torch
@@ -94,11 +95,6 @@ class DecodeRunner:
         self.shared_set = torch.zeros(G_, Bsz, w.hkv, self.set_cap, dtype=i32, device=dev)
         self.shared_len = torch.zeros(G_, Bsz, w.hkv, dtype=i32, device=dev)
         self.anchor_step = [None] * G_
-        # the groups' and steps' views of the state above, made once
-        self.lens_at = list(self.seq_lens.unbind(0))
-        self.topk_of = list(zip(self.topk_idx.unbind(0), self.topk_len.unbind(0)))
-        self.anchor_of = list(zip(self.anchor_set.unbind(0), self.anchor_len.unbind(0)))
-        self.shared_of = list(zip(self.shared_set.unbind(0), self.shared_len.unbind(0)))
         kv0 = self.kv[0][0]
         self.ws_select = B.workspace(B.prhs_workspace_size(B.PRHS_OP_SELECT, kv0, self.params), dev)
         self.ws_attn = B.workspace(
@@ -125,6 +121,24 @@ class DecodeRunner:
         return [B.prhs_psaw_first_visible(ps, n + j + 1) for n in self.w.n_ctx]
 
     # -- pieces -------------------------------------------------------------
+    # the steps' and groups' views of the state, made once, by the first call
+    # that needs them (a runner of dense steps needs none)
+    @functools.cached_property
+    def lens_at(self):
+        return self.seq_lens.unbind(0)
+
+    @functools.cached_property
+    def topk_of(self):
+        return list(zip(self.topk_idx.unbind(0), self.topk_len.unbind(0)))
+
+    @functools.cached_property
+    def anchor_of(self):
+        return list(zip(self.anchor_set.unbind(0), self.anchor_len.unbind(0)))
+
+    @functools.cached_property
+    def shared_of(self):
+        return list(zip(self.shared_set.unbind(0), self.shared_len.unbind(0)))
+
     def refresh(self, gi, j):
         l = gi * self.w.G
         if self.per_step_sets or not self.reuses:
