@@ -11,13 +11,16 @@ The extension ``_prhs_host`` makes the same checks and the call in native code
 (an attention call is enqueued in 4.2 us with it, in 12.9 from Python and
 ctypes).  It answers None where a check does not hold or an argument is of
 another kind (a tensor subclass, a number that is not a plain float or int);
-the Python code below then raises, or makes the call.
+the Python code below then raises, or makes the call.  Where the extension is
+not built, or was built for another Python, torch or libprhs, the Python code
+makes every call.
 """
 
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from ctypes import addressof
 
 import torch
@@ -105,6 +108,24 @@ _HOST_ENTRIES = [
 ]
 
 
+def _load_host(L):
+    """The extension _prhs_host bound to the library L, or None, with a warning,
+    where it is not built or was built for another Python, torch or libprhs."""
+    try:
+        from . import _prhs_host as h
+        made_for = (getattr(h, "torch_version", None), getattr(h, "abi_version", None))
+        here = (str(torch.__version__), L.prhs_abi_version())
+        if made_for == here:
+            h.bind(*(ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in _HOST_ENTRIES))
+            return h
+        why = f"built for torch {made_for[0]} and library version {made_for[1]}, not {here[0]} and {here[1]}"
+    except (ImportError, TypeError) as e:
+        why = str(e)
+    warnings.warn(f"calls go through ctypes, without the _prhs_host extension ({why}); "
+                  "`python -m paper_2602_08329_amd.build` builds it", RuntimeWarning, stacklevel=3)
+    return None
+
+
 def lib():
     """The loaded libprhs; raises if it has not been built."""
     global _lib, _host
@@ -162,13 +183,7 @@ def lib():
         L.prhs_psaw_first_visible.argtypes = [P(PrhsPsaw), i32]
         L.prhs_last_error.restype = ctypes.c_char_p
         L.prhs_last_error.argtypes = []
-        try:
-            from . import _prhs_host
-        except ImportError as e:
-            raise RuntimeError("the _prhs_host extension is missing: build it with "
-                               "`python -m paper_2602_08329_amd.build`") from e
-        _prhs_host.bind(*(ctypes.cast(getattr(L, n), vp).value for n in _HOST_ENTRIES))
-        _host = _prhs_host
+        _host = _load_host(L)
         _lib = L
     return _lib
 

@@ -1,5 +1,7 @@
 """Builds libprhs.so (HIP for gfx950) in-tree with hipcc, and the CPython
-extension _prhs_host.so (the binding's marshalling, no device code) with g++.
+extension _prhs_host (the binding's marshalling, no device code) with g++.  The
+extension is optional: without g++ or the headers it needs it is left out, with
+a message, and the binding makes its calls through ctypes.
 
     python -m paper_2602_08329_amd.build [-v]
     python -m paper_2602_08329_amd.build --host-sanitize OUT.so
@@ -29,7 +31,8 @@ LIB = os.path.join(PKG, "libprhs.so")
 SOURCES = ["prhs_api.hip", "select.hip", "dilate.hip", "attention.hip", "gate.hip", "prefill.hip"]
 
 HOST_SOURCE = "host_binding.cpp"
-HOST_LIB = os.path.join(PKG, "_prhs_host.so")
+# with the interpreter's ABI tag, so that another Python does not load it
+HOST_LIB = os.path.join(PKG, "_prhs_host" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 ARCH = "gfx950"
 FLAGS = [
@@ -60,17 +63,27 @@ SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=unde
 
 def host_command(out):
     """The g++ line of the binding's extension, against torch's headers and the
-    libraries `import torch` has loaded."""
+    libraries `import torch` has loaded; None (with a message) where something
+    it needs is missing."""
     import torch
     from torch.utils import cpp_extension
     cc = shutil.which("g++")
-    if cc is None:
-        raise RuntimeError("g++ not found; the binding's extension cannot be built")
+    py_inc = sysconfig.get_paths()["include"]
+    inc = cpp_extension.include_paths()
+    missing = [] if cc else ["g++"]
+    for folders, header in (([py_inc], "Python.h"),
+                            (inc, os.path.join("torch", "csrc", "autograd", "python_variable.h"))):
+        if not any(os.path.exists(os.path.join(d, header)) for d in folders):
+            missing.append(header)
+    if missing:
+        print(f"the binding's extension is left out ({', '.join(missing)} not found): "
+              "calls go through ctypes", file=sys.stderr, flush=True)
+        return None
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    inc = [x for p in cpp_extension.include_paths() for x in ("-isystem", p)]
     return [cc, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc,
-            "-I", sysconfig.get_paths()["include"], "-I", INCLUDE,
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f'-DPRHS_TORCH_VERSION="{torch.__version__}"',
+            *(x for p in inc for x in ("-isystem", p)), "-I", py_inc, "-I", INCLUDE,
             os.path.join(CSRC, HOST_SOURCE), "-o", out, "-L", lib, "-ltorch_python", "-ltorch_cpu",
             "-lc10"]
 
@@ -97,8 +110,9 @@ def build(verbose: bool = False, host_sanitize: str = None) -> str:
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
                                             text=True)))
     host_tmp = HOST_LIB + ".tmp"
-    if host_sanitize is None:
-        cmd = host_command(host_tmp)
+    host_cmd = host_command(host_tmp) if host_sanitize is None else None
+    if host_cmd is not None:
+        cmd = host_cmd
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((HOST_SOURCE, subprocess.Popen(cmd, stdout=subprocess.PIPE,
@@ -121,8 +135,10 @@ def build(verbose: bool = False, host_sanitize: str = None) -> str:
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout)
     os.replace(tmp, out_lib)
-    if host_sanitize is None:
+    if host_cmd is not None:
         os.replace(host_tmp, HOST_LIB)
+    elif host_sanitize is None and os.path.exists(HOST_LIB):
+        os.remove(HOST_LIB)   # of an earlier build
     return out_lib
 
 

@@ -372,4 +372,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_prhs_host", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__prhs_host() { return PyModule_Create(&module); }
+// torch_version and abi_version: what this was compiled against, for the
+// binding to compare with what is loaded.
+PyMODINIT_FUNC PyInit__prhs_host() {
+  PyObject* m = PyModule_Create(&module);
+  if (m && (PyModule_AddStringConstant(m, "torch_version", PRHS_TORCH_VERSION) < 0 ||
+            PyModule_AddIntConstant(m, "abi_version", PRHS_ABI_VERSION) < 0))
+    Py_CLEAR(m);
+  return m;
+}
