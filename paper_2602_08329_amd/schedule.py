@@ -121,8 +121,18 @@ class DecodeRunner:
         return [B.prhs_psaw_first_visible(ps, n + j + 1) for n in self.w.n_ctx]
 
     # -- pieces -------------------------------------------------------------
-    # the steps' and groups' views of the state, made once, by the first call
-    # that needs them (a runner of dense steps needs none)
+    # the steps' and groups' views of the state, made by the first call that
+    # needs them (a runner of dense steps needs none) and dropped where the
+    # attribute they are of is bound to another tensor: every call uses the
+    # runner's present state
+    _VIEWS_OF = {"seq_lens": "lens_at", "topk_idx": "topk_of", "topk_len": "topk_of",
+                 "anchor_set": "anchor_of", "anchor_len": "anchor_of",
+                 "shared_set": "shared_of", "shared_len": "shared_of"}
+
+    def __setattr__(self, name, value):
+        super().__setattr__(name, value)
+        self.__dict__.pop(self._VIEWS_OF.get(name), None)
+
     @functools.cached_property
     def lens_at(self):
         return self.seq_lens.unbind(0)
