@@ -915,21 +915,49 @@ int env_int(const char* name, int dflt) {
   return x > 0 ? x : dflt;
 }
 
-// Most workgroups of a launch: one per CU for sets, and for a dense stream
-// short enough that the merge of more splits costs more than it gains (1 x 8
-// units of 4000 rows at d 128 18.1 us with 1024, 10.9 with 256; 16 of 8000
-// 23.4 and 18.9, 4 of 38800 34.8 and 22.5); two, all resident together, for a
-// longer one (8 units of 32000 rows, 131 MB: 256, 512 and 1024 workgroups 33.3,
-// 31.3 and 35.9 us, 80 of 9000 68.5, 65.8 and 67.1).  fp32 dense: below.
-// PRHS_ATTN_GROUPS and PRHS_ATTN_DENSE_GROUPS override them (tuning knobs,
-// read once per process).
+// Most workgroups of a launch: one per CU for sets; for a dense bf16 stream of
+// few units one per CU where it is short enough that the merge of more splits
+// costs more than it gains (1 x 8 units of 4000 rows at d 128 18.1 us with
+// 1024, 10.9 with 256; 16 of 8000 23.4 and 18.9, 4 of 38800 34.8 and 22.5),
+// two, all resident together, for a longer one (8 units of 32000 rows, 131 MB:
+// 256, 512 and 1024 workgroups 33.3, 31.3 and 35.9 us, 80 of 9000 68.5, 65.8
+// and 67.1).  PRHS_ATTN_GROUPS and PRHS_ATTN_DENSE_GROUPS override them (tuning
+// knobs, read once per process).
 constexpr long long kLongDenseBytes = 96LL << 20;
+constexpr long long kDenseGroups = 1024;
+long long dense_groups_override() {
+  static const int v = env_int("PRHS_ATTN_DENSE_GROUPS", 0);
+  return v;
+}
 long long target_groups(int dtype, bool dense, long long bytes) {
   static const int sparse_v = env_int("PRHS_ATTN_GROUPS", 256);
-  static const int dense_v = env_int("PRHS_ATTN_DENSE_GROUPS", 0);
   if (!dense) return sparse_v;
-  if (dense_v) return dense_v;
-  return dtype != 1 ? 1024 : (bytes < kLongDenseBytes ? 256 : 512);
+  if (dense_groups_override()) return dense_groups_override();
+  return dtype != 1 ? kDenseGroups : (bytes < kLongDenseBytes ? 256 : 512);
+}
+
+// Splits of a dense bf16 stream of many units (more than half the CUs): none
+// where a workgroup can stage a unit's rows, as that saves the merge launch
+// (192 units of 1719 rows at d 128 26.5 us, in two splits 31.4; 224 of 1855
+// 37.4 and 42.0; 400 of 490 22.7 and 34.6), except on up to a quarter more units
+// than CUs of kLongUnitBytes or more of K and V, where the CUs that take two
+// of them keep the rest waiting (300 units of 1606 rows 43.9 us, in four
+// splits 39.3; 257 of 1142 35.4 and 32.0; 300 of 990 at d 64, 250 KB, 20.2
+// and 22.9).  Split, a launch has about kDenseGroups workgroups, which even out
+// ragged lengths (240 ragged units of 2801 rows: 480 workgroups 50.8 us, 1200
+// 48.2; 256 of 8385 2048 workgroups 151, 1280 137), but not a few more than fill
+// the kDenseSlots places for one a whole number of times (136 units of 11811
+// rows: 1088 workgroups 119 us, 952 104; units a few more than the CUs are better
+// off with the finer splits, 260 of 5488 in three 130, in four 125).
+constexpr long long kLongUnitBytes = 320LL << 10;
+constexpr long long kDenseSlots = 512;   // two workgroups a CU
+long long many_unit_splits(long long units, long long rows, int d, long long cmax) {
+  const long long least = (rows + cmax - 1) / cmax;
+  const bool few_over = units > 256 && units <= 320;
+  if (least == 1 && !(few_over && rows * d * 4 >= kLongUnitBytes)) return 1;
+  const long long k = std::max(least, (kDenseGroups + units - 1) / units);
+  const long long over = units * k % kDenseSlots;
+  return !few_over && over > 0 && over <= kDenseSlots / 4 && k > least ? k - 1 : k;
 }
 
 // Waves per bf16 workgroup: PRHS_ATTN_WAVES overrides the default of 4.
@@ -1030,7 +1058,8 @@ int waves_for(int dtype, bool dense, long long groups, int chunk) {
 // units of 1200 rows 32.6 and 27.3, 80 of 1500 23.3 and 21.2).  Where the
 // rows staged per workgroup, 8 per thread, allow no such split, sets take the
 // fewest splits they allow and a dense stream twice the workgroups and so on
-// (16 units of 65537 rows: 528 workgroups 105 us, 1008 92).
+// (16 units of 65537 rows: 528 workgroups 105 us, 1008 92).  Dense bf16 streams
+// of many units: many_unit_splits.
 void attn_split_geometry(int dtype, bool dense, int batch, int hq, int hkv, int d, int rows_cap,
                          int* chunk, int* nsplit) {
   const int gran = dtype == 1 ? 32 : 16;
@@ -1045,6 +1074,10 @@ void attn_split_geometry(int dtype, bool dense, int batch, int hq, int hkv, int 
   long long tg = target_groups(dtype, dense, rows * units * d * 4);
   while (dense && rows_of(tg) > cmax) tg *= 2;
   long long c = rows_of(tg);
+  if (dense && dtype == 1 && units > 128 && !dense_groups_override()) {
+    const long long k = many_unit_splits(units, rows, d, cmax);
+    c = (rows + k - 1) / k;
+  }
   const long long cmin = (rows + kMaxSplits - 1) / kMaxSplits;
   if (dtype != 1) {
     c = std::max(c, std::min((rows + kMergeSplitsF32 - 1) / kMergeSplitsF32, rows_of(256)));

@@ -1,0 +1,52 @@
+"""How the decode attention launches divide their rows, read on the host from
+the workspace a call asks for (its split-K partials): no device work."""
+
+import ctypes
+import re
+
+import pytest
+
+from paper_2602_08329_amd import binding as B
+
+CUS = 256
+
+
+def kv(dtype, batch, hq, hkv, d, rows):
+    return B.PrhsKv(batch, hq, hkv, d, B.PRHS_BF16 if dtype == "bf16" else B.PRHS_F32,
+                    B.PRHS_KV_CONTIGUOUS, rows, 0, 0, 0, 0x1000, 0x2000, None, 0x3000, rows)
+
+
+def need(dtype, batch, hq, hkv, d, rows, dense):
+    """Bytes of workspace the call needs, from its refusal of none."""
+    L, c = B.lib(), kv(dtype, batch, hq, hkv, d, rows)
+    if dense:
+        st = L.prhs_dense_decode_attn(ctypes.byref(c), 0x10, 1.0, 0x20, None, None, 0, None)
+    else:
+        st = L.prhs_sparse_decode_attn(ctypes.byref(c), 0x10, 0x20, 0x30, rows, 1.0, 0x40, None, None,
+                                       0, None)
+    assert st == B.PRHS_E_WORKSPACE
+    return int(re.search(rb"workspace of (\d+) bytes", L.prhs_last_error()).group(1))
+
+
+def splits(dtype, batch, hq, hkv, d, rows, dense):
+    """Splits a unit: partials of d + 2 floats, the outputs rounded up to 256 bytes."""
+    n = need(dtype, batch, hq, hkv, d, rows, dense)
+    return n // (batch * hq * (d + 2) * 4)
+
+
+@pytest.mark.parametrize("batch,hkv,d,rows,want", [
+    # 129 to 256 units: no split while a workgroup stages the rows
+    (129, 1, 128, 2048, 1), (192, 1, 128, 1700, 1), (32, 8, 128, 1989, 1), (31, 8, 64, 2048, 1),
+    # a few more units than CUs: unsplit while short, else about 1024 workgroups
+    (257, 1, 128, 600, 1), (300, 1, 64, 990, 1), (257, 1, 128, 1142, 4), (40, 8, 128, 1606, 4),
+    (264, 1, 64, 1367, 4), (321, 1, 128, 1606, 1), (100, 8, 128, 2000, 1),
+    # rows beyond one workgroup: about 1024 workgroups, not a few over a multiple
+    # of 512, and at least what staging needs
+    (240, 1, 128, 2801, 5), (192, 1, 128, 2953, 5), (32, 8, 128, 8385, 5), (288, 1, 128, 3505, 4), (352, 1, 128, 2122, 2),
+    (136, 1, 128, 11811, 7), (72, 8, 128, 3642, 2), (75, 8, 128, 9000, 5),
+    # few units: one workgroup a CU for a short stream, two for a long one
+    (128, 1, 128, 1400, 2), (2, 8, 128, 65536, 32), (1, 8, 128, 4000, 32), (1, 8, 128, 32768, 64),
+])
+def test_dense_bf16_splits(batch, hkv, d, rows, want):
+    for g in (1, 4):
+        assert splits("bf16", batch, hkv * g, hkv, d, rows, True) == want
