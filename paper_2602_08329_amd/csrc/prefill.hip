@@ -40,11 +40,9 @@
 // group's products beside the other's softmax) took the same cycles; dot
 // products for the remainders p - hi were slower, and raised issue priority
 // for the products changed nothing.
-#include <math.h>
-
-#include <algorithm>
 #include <type_traits>
 
+#include "prefill_plan.h"
 #include "prhs_internal.h"
 
 namespace prhs {
@@ -58,17 +56,6 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-// Waves of a workgroup: two or three a SIMD, as many as their registers allow.
-constexpr int waves_of(int w) { return w == 32 ? 8 : 12; }
-// A second workgroup on the CU: at d 64, where 128 registers a wave do without
-// scratch (126 with 8 spilled for the paged one-sided form: 2 us more a launch).
-constexpr bool two_per_cu(int d, int w, int ns, bool paged) { return d == 64 && w == 32 && (ns == 1 ? !paged : ns == 4 && paged); }
-constexpr int waves_per_simd(int d, int w, int ns, bool paged) {
-  return (two_per_cu(d, w, ns, paged) ? 2 : 1) * waves_of(w) / 4;
-}
-constexpr int kQueries = 256;  // queries per workgroup of 32-query waves with one key side
-constexpr int kPackBlocks = 48;  // blocks a unit up to which a launch's packing is worked out
-constexpr int kXcds = 8;      // accelerator dies, each with its own L2
 constexpr float kLn2 = 0.69314718055994530942f;
 constexpr float kLazyLog2 = 8.f;  // log2 of the largest probability between rescales
 
@@ -78,6 +65,7 @@ struct PrefillArgs {
   int T;
   int qblock;             // queries per workgroup
   int qfirst;             // queries of a unit's first workgroup
+  int group;              // units of an XCD worked through side by side
   int psaw;               // nonzero: row i attends [0, sink) U [first visible at i + 1, i]
   double psaw_f;          // Eq. psaw factor of the layer
   int sink;
@@ -365,26 +353,6 @@ __device__ __forceinline__ void tile_products(const VFrag<D, W>& V, const Probs<
   }
 }
 
-// Query block and (batch, head) unit of workgroup L.  Workgroups go to the 8
-// XCDs round-robin by id.  When the units divide over the XCDs, XCD x works
-// through its own units in groups of kUnitGroup, within a group longest
-// blocks first over all of its units: a unit's K and V stay in one L2, its
-// blocks run side by side, and the launch ends with the short blocks.
-// Otherwise all units form one group.
-constexpr int kUnitGroup = 4;
-__device__ __forceinline__ void block_of(int units, int nqb, int L, int* bh, int* qb) {
-  if (units % kXcds == 0) {
-    const int per = units / kXcds, x = L % kXcds, i = L / kXcds;
-    const int grp = i / (kUnitGroup * nqb), j = i - grp * (kUnitGroup * nqb);
-    const int gu = min(kUnitGroup, per - grp * kUnitGroup);
-    *bh = x * per + grp * kUnitGroup + j % gu;
-    *qb = nqb - 1 - j / gu;
-  } else {
-    *bh = L % units;
-    *qb = nqb - 1 - L / units;
-  }
-}
-
 template <int D, int W, int NS, bool PAGED>
 __global__ __launch_bounds__(64 * waves_of(W)) __attribute__((amdgpu_waves_per_eu(waves_per_simd(D, W, NS, PAGED), waves_per_simd(D, W, NS, PAGED))))
 void attn_prefill_bf16(PrefillArgs a) {
@@ -403,7 +371,7 @@ void attn_prefill_bf16(PrefillArgs a) {
   // blocks of qblock queries (at most W QG), the first of qfirst
   const int nqb = 1 + (max(a.T - a.qfirst, 0) + a.qblock - 1) / a.qblock;
   int bh, qb;
-  block_of(a.kv.batch * a.kv.hq, nqb, (int)blockIdx.x, &bh, &qb);
+  block_of(a.kv.batch * a.kv.hq, nqb, a.group, (int)blockIdx.x, &bh, &qb);
   const int hq = a.kv.hq, G = hq / a.kv.hkv;
   const int b = bh / hq, h = bh % hq, g = h / G;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -613,122 +581,6 @@ void attn_prefill_bf16(PrefillArgs a) {
 
 }  // namespace
 
-// Time of a launch of `units` blocks of each of the n costs on `slots` places
-// for one block at a time, each block to the place that is free first: places
-// as groups of equal load, of which each cost splits at most one.
-static float packed_time(const float* cost, int n, long long units, long long slots) {
-  struct Group {
-    float load;
-    long long count;
-  };
-  Group g[kPackBlocks + 1];
-  int m = 1;
-  g[0] = {0.f, slots};
-  for (int i = 0; i < n; ++i) {
-    for (long long left = units; left > 0;) {
-      int lo = 0;
-      for (int j = 1; j < m; ++j) lo = g[j].load < g[lo].load ? j : lo;
-      const long long take = std::min(left, g[lo].count);
-      left -= take;
-      if (take == g[lo].count) {
-        g[lo].load += cost[i];
-      } else {
-        g[lo].count -= take;
-        g[m++] = {g[lo].load + cost[i], take};
-      }
-    }
-  }
-  float t = 0.f;
-  for (int j = 0; j < m; ++j) t = std::max(t, g[j].load);
-  return t;
-}
-
-// How a launch divides its units: waves of w queries, ns key sides, blocks of
-// qblock queries, the first of qfirst.
-struct Plan {
-  int w, ns, qblock, qfirst;
-};
-
-// The plan of least time, its blocks packed on the CUs.  A block costs
-// `step` for each of its key tiles (64, 64, 128 and 128 keys) and `fixed`
-// once (for a prompt of T tokens), in us; a step costs by the waves that share a SIMD, as it is their
-// issue and the chain of one wave that it waits for.  Fitted to 2600 timed
-// launches (within 6% on average; the plan taken is 2% from the best of its
-// launch).  What each is for, d 128, in us, with (16 queries, one side | 32
-// queries, one | two | four sides):
-//   256 queries fill the LDS reads best, on launches of many blocks: 32 heads
-//   x 4096 - | 187 | 216 | 273, 128 x 450 33.2 | 30.1 | 36.2 | 47.7;
-//   sides shorten the longest block of few units: 32 x 537 20.8 | 23.6 | 20.6
-//   | 17.6, 4 x 8000 - | 279 | 171 | 123;
-//   three narrow waves a SIMD hide a chain that two leave bare, where a CU
-//   gets about one block: 128 x 265 15.6 | 16.8 | 22.9 | 27.2, 128 x 173 11.6
-//   | 12.9 | 13.0 | 20.5, 16 x 6000 213 | 228 | - | -.
-// The first block may differ from the others, and the last be short: it sees
-// the most keys (256 x 536 at 32 queries 68.2 with even blocks, 64.4 with 128
-// first and then 256; 128 x 316 at 16 queries 19.0 even, 17.9 with 192 first).  At d 64 a second
-// workgroup of the wide waves fits a CU where 128 registers hold them: 256 x
-// 1024 99 -> 79, 64 x 7777 834 -> 731.
-static Plan plan_of(const PrefillLaunch& s, long long units, int cus) {
-  const int T = s.T, d = s.kv.d;
-  const bool paged = s.kv.paged;
-  const auto whole = [](int q, int w) { return (q + w - 1) / w * w; };
-  const int nwide = (T + kQueries - 1) / kQueries;
-  if (cus <= 0 || nwide * units >= 8LL * cus)
-    return {32, 1, kQueries, whole(T - (nwide - 1) * kQueries, 32)};
-  // one block, one tile or two: the wave's chain is all there is (64 x 113 8.4
-  // with 16 queries, 8.8, 10.0 and 8.7)
-  if (d == 128 && T <= 128 && units <= cus) return {16, 1, whole(T, 16), whole(T, 16)};
-  struct Cost {
-    float step[3], fixed;
-  };
-  // d 128, d 64, d 64 paged; the last of each is the one that shares a CU,
-  // where the launch has more blocks than CUs
-  static const Cost costs[3][5] = {
-      {{{1.27f, 1.62f, 2.12f}, 6.17f}, {{2.03f, 2.65f}, 5.80f}, {{1.86f, 2.92f}, 7.54f}, {{0.92f, 1.70f}, 7.43f}, {}},
-      {{{1.40f, 1.47f, 1.72f}, 3.95f}, {{1.67f, 2.00f}, 3.91f}, {{1.59f, 2.25f}, 4.86f}, {{0.56f, 1.19f}, 4.65f},
-       {{1.65f, 2.80f}, 6.94f}},
-      {{{1.04f, 1.47f, 1.68f}, 4.65f}, {{1.74f, 2.08f}, 4.73f}, {{1.66f, 2.20f}, 5.81f}, {{1.36f, 1.62f}, 5.34f},
-       {{1.18f, 1.80f}, 6.94f}}};
-  const Cost* const table = costs[d == 128 ? 0 : paged ? 2 : 1];
-  Plan best = {32, 1, kQueries, kQueries};
-  float least = INFINITY;
-  for (int v = 0; v < 4; ++v) {
-    const int w = v == 0 ? 16 : 32, ns = v == 0 ? 1 : 1 << (v - 1), kt = v < 2 ? 64 : 128;
-    const int most = w * waves_of(w) / ns, nmin = (T + most - 1) / most;
-    const int sizes[4] = {whole((T + nmin - 1) / nmin, w), whole((T + nmin) / (nmin + 1), w), most,
-                          v == 3 ? most : most / 2};
-    // each size with what is left over in the first block, then in the last
-    for (int k = nmin > 16 ? 4 : 0; k < (nmin > 16 ? 6 : 8); ++k) {
-      const int qb = sizes[k / 2];
-      const int n = k % 2 ? (T + qb - 1) / qb : 1 + (std::max(T - most, 0) + qb - 1) / qb;
-      const int qf = k % 2 ? qb : std::min(most, whole(T - (n - 1) * qb, w));
-      const bool shared = two_per_cu(d, w, ns, paged) && n * units > cus;
-      const Cost& c = table[shared ? 4 : v];
-      const long long slots = shared ? 2LL * cus : cus;
-      float cost[kPackBlocks], sum = 0.f, longest = 0.f;
-      for (int j = n - 1; j >= 0; --j) {  // longest first
-        const int end = std::min(T, qf + j * qb), q0 = j ? qf + (j - 1) * qb : 0;
-        int tiles = (end + kt - 1) / kt;
-        if (s.psaw) {
-          const int nsink = (std::min(s.sink, end) + kt - 1) / kt;
-          const int first = psaw_first_visible(s.psaw_f, s.sink, q0 + 1);
-          tiles = std::min(tiles, nsink + std::max(tiles - std::max(first / kt, nsink), 0));
-        }
-        const int waves = (end - q0 + w - 1) / w * ns;
-        const float t = c.step[(waves + 3) / 4 - 1] * (float)tiles + c.fixed;
-        if (n <= kPackBlocks) cost[n - 1 - j] = t;
-        sum += t;
-        longest = std::max(longest, t);
-      }
-      // many blocks pack evenly
-      const float t = n > kPackBlocks ? std::max(longest, sum * (float)units / (float)slots)
-                                      : packed_time(cost, n, units, slots);
-      if (t < least) least = t, best = {w, ns, qb, qf};
-    }
-  }
-  return best;
-}
-
 hipError_t launch_prefill(const PrefillLaunch& s, hipStream_t stream) {
   if (s.kv.batch == 0 || s.T == 0) return hipSuccess;
   PrefillArgs a;
@@ -742,10 +594,13 @@ hipError_t launch_prefill(const PrefillLaunch& s, hipStream_t stream) {
   a.out = s.out;
   a.lse = s.lse;
   const long long units = (long long)s.kv.batch * s.kv.hq;
-  const Plan plan = plan_of(s, units, device_cus());
+  const int cus = device_cus();
+  const PrefillPlan plan = plan_of({s.T, s.kv.d, s.kv.paged, s.psaw, s.psaw_f, s.sink}, units, cus);
+  const int nqb = plan.blocks(s.T);
   a.qblock = plan.qblock;
   a.qfirst = plan.qfirst;
-  const dim3 grid((unsigned)((1 + (std::max(s.T - a.qfirst, 0) + a.qblock - 1) / a.qblock) * units));
+  a.group = unit_group((int)(units / kXcds), nqb, cus);
+  const dim3 grid((unsigned)(nqb * units));
 #define PRHS_PREFILL_GO(DV, W, NS, PG) \
   hipLaunchKernelGGL((attn_prefill_bf16<DV, W, NS, PG>), grid, dim3(64 * waves_of(W)), 0, stream, a)
 #define PRHS_PREFILL_LAUNCH(DV, PG)                        \
