@@ -119,8 +119,19 @@ struct PrefillPlan {
 // The first block may differ from the others, and the last be short: it sees
 // the most keys (256 x 536 at 32 queries 68.2 with even blocks, 64.4 with 128
 // first and then 256; 128 x 316 at 16 queries 19.0 even, 17.9 with 192 first).
-// At d 64 a second workgroup of the wide waves fits a CU where 128 registers hold
-// them: 256 x 1024 99 -> 79, 64 x 7777 834 -> 731.
+// Prompts of more than kShortBlocks blocks put what is left over in the last (8 x
+// 12197 at 16 queries 433, in the first 466).  At d 64 a second workgroup of the
+// wide waves fits a CU where 128 registers hold them: 256 x 1024 99 -> 79, 64 x
+// 7777 834 -> 731.
+// Every layer of a model asks for its plan, so its work is bounded: prompts of
+// more than kPackBlocks blocks are summed over that many of them, and a form is
+// packed only where an even spread of its blocks would win (on one CPU, us: 40
+// units x 2000 17.8 -> 2.6, 32 x 4096 5.3 -> 2.4, one unit x 131072 79 -> 1.3).
+constexpr int kShortBlocks = 16;
+// Key sides on launches of more than two rounds of blocks take longer than the sum
+// of their blocks (d 128, 8 units x 11000 362 us by the sum, 400 timed, 16
+// queries 359; under a window 8 x 10611 287, 319 and 285).
+constexpr float kSidesLate = 1.05f;
 inline PrefillPlan plan_of(const PrefillShape& s, long long units, int cus) {
   const int T = s.T, d = s.d;
   const bool paged = s.paged != 0;
@@ -152,7 +163,7 @@ inline PrefillPlan plan_of(const PrefillShape& s, long long units, int cus) {
     const int sizes[4] = {whole((T + nmin - 1) / nmin, w), whole((T + nmin) / (nmin + 1), w), most,
                           v == 3 ? most : most / 2};
     // each size with what is left over in the first block, then in the last
-    for (int k = nmin > 16 ? 4 : 0; k < (nmin > 16 ? 6 : 8); ++k) {
+    for (int k = nmin > kShortBlocks ? 5 : 0; k < (nmin > kShortBlocks ? 6 : 8); ++k) {
       const int qb = sizes[k / 2];
       const int n = k % 2 ? (T + qb - 1) / qb : 1 + (std::max(T - most, 0) + qb - 1) / qb;
       const int qf = k % 2 ? qb : std::min(most, whole(T - (n - 1) * qb, w));
@@ -171,15 +182,23 @@ inline PrefillPlan plan_of(const PrefillShape& s, long long units, int cus) {
         return c.step[(waves + 3) / 4 - 1] * (float)tiles + c.fixed;
       };
       float cost[kPackBlocks], sum = 0.f, longest = 0.f;
-      for (int j = n - 1; j >= 0; --j) {  // longest first
-        const float t = time_of(j);
-        if (n <= kPackBlocks) cost[n - 1 - j] = t;
-        sum += t;
-        longest = std::max(longest, t);
+      if (n <= kPackBlocks) {
+        for (int j = n - 1; j >= 0; --j) {  // longest first
+          const float t = cost[n - 1 - j] = time_of(j);
+          sum += t;
+          longest = std::max(longest, t);
+        }
+      } else {  // every skip-th block, from the middle of the first skip; the last may be short
+        const int skip = (n + kPackBlocks - 1) / kPackBlocks;
+        int m = 0;
+        for (int j = skip / 2; j < n; j += skip, ++m) sum += time_of(j);
+        sum *= (float)n / (float)m;
+        longest = std::max(time_of(n - 1), time_of(n - 2));
       }
-      // many blocks pack evenly
-      const float t = n > kPackBlocks ? std::max(longest, sum * (float)units / (float)slots)
-                                      : packed_time(cost, n, units, slots);
+      // no packing is shorter than an even spread, and many blocks pack evenly
+      const float more = ns > 1 && n * units > 2 * slots ? kSidesLate : 1.f;
+      float t = more * std::max(longest, sum * (float)units / (float)slots);
+      if (t < least && n <= kPackBlocks) t = more * packed_time(cost, n, units, slots);
       if (t < least) least = t, best = {w, ns, qb, qf};
     }
   }

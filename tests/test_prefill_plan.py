@@ -1,7 +1,9 @@
 """How prefill launches divide their prompts (prefill_plan.h), on the host: the
 header compiled into a small program and asked."""
 
+import math
 import os
+import random
 import shutil
 import subprocess
 
@@ -63,3 +65,40 @@ def test_groups_hold_enough_blocks_to_end_a_launch_evenly(ask):
         assert groups == 1 or last >= g - groups + 1
         # and no more than it takes
         assert g * nqb < 2 * (128 + nqb) or g == 1
+
+
+# ---------------------------------------------------------------- the plan
+
+def shape(T, units, d=128, paged=0, psaw=0, factor=0.0, sink=4, cus=256):
+    return f"{T} {units} {d} {paged} {psaw} {factor:.17g} {sink} {cus}"
+
+
+def test_plans_cover_their_prompts(ask):
+    rng = random.Random(5)
+    shapes = []
+    for _ in range(3000):
+        T = int(math.exp(rng.uniform(0, math.log(200000))))
+        units = int(math.exp(rng.uniform(0, math.log(3000))))
+        psaw = rng.randrange(2)
+        shapes.append((T, units, rng.choice([64, 128]), rng.randrange(2), psaw, rng.random() * 0.95 * psaw,
+                       rng.choice([0, 4, 300]), rng.choice([256, 256, 32, 0])))
+    for s, r in zip(shapes, ask(["plan " + shape(*s) for s in shapes])):
+        w, ns, qb, qf, n = map(int, r)
+        assert (w, ns) in ((16, 1), (32, 1), (32, 2), (32, 4)), s
+        most = w * (12 if w == 16 else 8) // ns   # queries of a workgroup's waves
+        assert 0 < qb <= most and 0 < qf <= most and qb % w == 0 and qf % w == 0, (s, r)
+        assert qf + (n - 1) * qb >= s[0] and (n == 1 or qf + (n - 2) * qb < s[0]), (s, r)
+
+
+def test_work_of_a_plan_is_bounded(ask):
+    # every layer of a model asks for one: long prompts of few units, whose
+    # blocks are many, cost no multiple of what a prompt of 48 blocks does
+    short, *long = (float(r[0]) for r in ask(
+        ["time " + shape(*a) for a in ((2900, 4), (24000, 4), (131072, 1), (131072, 1, 64, 1, 1, 0.3))]))
+    assert max(long) <= 3 * short, (short, long)
+
+
+def test_left_over_queries_of_a_long_prompt_come_last(ask):
+    # 64 blocks for 32 CUs an XCD; and queries, not key sides, where two a CU follow
+    assert [r[:4] for r in ask(["plan " + shape(12197, 8), "plan " + shape(11000, 8),
+                                "plan " + shape(10611, 8, 128, 0, 1, 0.2)])] == [["16", "1", "192", "192"]] * 3
