@@ -56,15 +56,24 @@ constexpr int kMaxWaves = 8;        // waves of an attention workgroup
 // Sparse sets of at most this many rows per unit are not split: a launch of
 // one workgroup per unit beats a split launch plus its merge launch (fp32
 // rows are twice as long: 32 units of 500 rows 20.7 us unsplit, 13.4 split; 4
-// units of 150 rows 5.6 and 7.9).
+// units of 150 rows 5.6 and 7.9).  Dense fp32 streams the same, and up to
+// kNoSplitManyF32 rows where kManyF32 units keep the chip busy (64 units of 16
+// heads over 146 rows at d 128 19.4 us in three splits, 11.4 unsplit, 48 of 338
+// 25.6 and 17.8), fewer where few units have many heads (kNoSplitHeadRowsF32 rows
+// times heads: 12 units of 16 heads over 219 rows 10.0 us in four splits, 11.6
+// unsplit; 32 of 8 over 203 9.0 and 7.4).
 constexpr int kNoSplitRows = 512;
 constexpr int kNoSplitRowsF32 = 256;
-// fp32 splits: at least kMinRowsF32 rows, and no more than kMergeSplitsF32 of
-// them per unit once the launch has 256 workgroups, since the merge reads
-// every split's output of every head (dense, 8 units of 4 heads at d 128:
-// 2000 rows in 125 splits 18.3 us, in 32 13.6; 8000 rows in 125 26.5, in 32
-// 19.8).
+constexpr int kNoSplitManyF32 = 450, kManyF32 = 40;
+constexpr int kNoSplitHeadRowsF32 = 2048;
+// fp32 splits: at least kMinRowsF32 rows (half of that where the splits of all
+// heads are fewer than kFewHeadsF32: one unit of 8 heads over 377 rows 8.7 -> 7.6
+// us), and no more than kMergeSplitsF32 of them per unit once the launch has 256
+// workgroups, since the merge reads every split's output of every head (dense, 8
+// units of 4 heads at d 128: 2000 rows in 125 splits 18.3 us, in 32 13.6; 8000
+// rows in 125 26.5, in 32 19.8).
 constexpr int kMinRowsF32 = 64;
+constexpr long long kFewHeadsF32 = 192;
 constexpr long long kMergeSplitsF32 = 32;
 
 struct AttnArgs {
@@ -998,13 +1007,17 @@ hipError_t launch_typed(const AttnArgs& a, int dtype, int units, int waves, hipS
     hipLaunchKernelGGL((attn_split_bf16<D, DENSE, PAGED>), dim3(a.nsplit, units), dim3(64 * waves),
                        dyn, stream, a);
   } else {
-    // heads per workgroup: all (up to 8), or fewer while the launch would
-    // leave CUs without a workgroup, where the heads' serial work costs more
-    // than reading the rows again from the caches (8 units of 8
-    // heads over 60 rows at d 64: 8 heads 8.0 us, 4 6.3, 2 5.8, 1 6.1)
+    // heads per workgroup: all (up to 8), or fewer while the launch has at most
+    // a wave for each of the four SIMDs of a CU, where the heads' serial work
+    // costs more than reading the rows again from the caches, and a workgroup a
+    // head where half the CUs get a wave at most (8 units of 8 heads over 60 rows
+    // at d 64: 8 heads 8.0 us, 4 6.3, 2 5.8, 1 6.1; 48 of 16 over 338 rows at d
+    // 128: 8 heads a workgroup 21, 4 17.8, 2 24; 112 of 16 over 82 rows 15.3,
+    // 20.0 and -; one of 8 over 377 rows in 12 splits 2 heads 8.8, 1 7.5)
     const int G = a.kv.hq / a.kv.hkv;
+    const long long row_waves = (long long)units * a.nsplit * waves;   // of one workgroup a split
     int gp = G == 1 ? 1 : (G == 2 ? 2 : (G <= 4 ? 4 : 8));
-    while (gp > 2 && (long long)units * a.nsplit * ((G + gp - 1) / gp) < device_cus()) gp >>= 1;
+    while (gp > 1 && row_waves * ((G + gp - 1) / gp) <= (gp > 2 ? 4 * device_cus() : device_cus() / 2)) gp >>= 1;
     const hipError_t e = gp == 1   ? launch_f32<D, 1, DENSE>(a, units, waves, stream)
                          : gp == 2 ? launch_f32<D, 2, DENSE>(a, units, waves, stream)
                          : gp == 4 ? launch_f32<D, 4, DENSE>(a, units, waves, stream)
@@ -1081,10 +1094,16 @@ void attn_split_geometry(int dtype, bool dense, int batch, int hq, int hkv, int 
   const long long cmin = (rows + kMaxSplits - 1) / kMaxSplits;
   if (dtype != 1) {
     c = std::max(c, std::min((rows + kMergeSplitsF32 - 1) / kMergeSplitsF32, rows_of(256)));
-    c = std::max<long long>(c, kMinRowsF32);
+    const long long least = std::max<long long>(c, kMinRowsF32);
+    const bool few = (rows + least - 1) / least * batch * hq < kFewHeadsF32 &&
+                     rows <= kMergeSplitsF32 * kMinRowsF32 / 2;
+    c = std::max<long long>(c, few ? kMinRowsF32 / 2 : kMinRowsF32);
   }
   if (c < cmin) c = cmin;
-  if (!dense && rows <= (dtype == 1 ? kNoSplitRows : kNoSplitRowsF32) && rows <= cmax) c = rows;
+  long long whole = dtype == 1 ? (dense ? 0 : kNoSplitRows) : kNoSplitRowsF32;
+  if (dense && dtype != 1)
+    whole = units >= kManyF32 ? kNoSplitManyF32 : std::min(whole, (long long)kNoSplitHeadRowsF32 * hkv / hq);
+  if (rows <= whole && rows <= cmax) c = rows;
   if (c > cmax) c = cmax;
   if (c < gran) c = gran;
   const long long ns = (rows + c - 1) / c;

@@ -34,6 +34,18 @@ def splits(dtype, batch, hq, hkv, d, rows, dense):
     return n // (batch * hq * (d + 2) * 4)
 
 
+def f32_heads(batch, hq, hkv, d, rows, dense):
+    """Query heads of a workgroup of the fp32 kernel on CUS CUs: the launch's rule,
+    again."""
+    ns, units, g = splits("f32", batch, hq, hkv, d, rows, dense), batch * hkv, hq // hkv
+    chunk = -(-(-(-rows // ns)) // 16) * 16
+    waves = min(8, -(-chunk // (16 if units * ns < 2 * CUS else 32)))
+    gp = 1 if g == 1 else 2 if g == 2 else 4 if g <= 4 else 8
+    while gp > 1 and units * ns * waves * -(-g // gp) <= (4 * CUS if gp > 2 else CUS // 2):
+        gp //= 2
+    return gp
+
+
 @pytest.mark.parametrize("batch,hkv,d,rows,want", [
     # 129 to 256 units: no split while a workgroup stages the rows
     (129, 1, 128, 2048, 1), (192, 1, 128, 1700, 1), (32, 8, 128, 1989, 1), (31, 8, 64, 2048, 1),
@@ -50,3 +62,18 @@ def splits(dtype, batch, hq, hkv, d, rows, dense):
 def test_dense_bf16_splits(batch, hkv, d, rows, want):
     for g in (1, 4):
         assert splits("bf16", batch, hkv * g, hkv, d, rows, True) == want
+
+
+@pytest.mark.parametrize("batch,hq,hkv,d,rows,dense,want", [
+    # short rows unsplit, sets and streams
+    (1, 4, 4, 64, 256, False, 1), (64, 1, 1, 64, 257, False, 4), (1, 4, 4, 64, 256, True, 1),
+    (1, 16, 1, 64, 128, True, 1), (6, 32, 2, 64, 129, True, 3),
+    (40, 16, 1, 128, 450, True, 1), (40, 16, 1, 128, 451, True, 8), (39, 1, 1, 128, 257, True, 5),
+    # few heads: splits of 32 rows up to 1024 of them, else of 64
+    (1, 8, 1, 128, 377, True, 12), (1, 2, 1, 64, 1024, False, 32), (1, 2, 1, 64, 1025, False, 17),
+    (12, 16, 1, 128, 1000, True, 16),
+    # at most 32 splits once the launch has 256 workgroups
+    (1, 8, 8, 128, 8000, False, 32), (2, 16, 8, 128, 8000, True, 32), (32, 8, 8, 128, 3000, True, 4),
+])
+def test_f32_splits(batch, hq, hkv, d, rows, dense, want):
+    assert splits("f32", batch, hq, hkv, d, rows, dense) == want

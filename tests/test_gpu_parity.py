@@ -869,9 +869,10 @@ def test_select_off_grid_within_rounding_of_threshold(name):
 # ---------------------------------------------------------------- fp32 groups
 
 F32_GROUPS = [
-    # hq, hkv, d, paged, lens: query groups of every size class of the fp32
-    # kernels (1, 2, up to 4, up to 8, two workgroups of up to 8), lengths
-    # around their steps (8 or 16 rows), splits (64 rows) and wave runs (64 keys)
+    # hq, hkv, d, paged, lens: groups of 1, 3, 5, 8, 9 and 16 query heads on
+    # launches small enough that an attention workgroup takes four of them at
+    # most (test_gpu_attention_splits.py has the wider ones), lengths around the
+    # kernels' steps (8 or 16 rows), splits (64 rows) and wave runs (64 keys)
     (2, 2, 128, False, (1, 7, 63, 65)),
     (6, 2, 128, True, (16, 255, 257, 2049)),
     (5, 1, 64, False, (64, 1023, 1025)),
