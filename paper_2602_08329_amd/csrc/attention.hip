@@ -34,8 +34,8 @@
 // order; the dimension order inside a row is permuted identically on K and
 // Q.  V needs no transpose: a lane's 8 rows x 8 dims block feeds the second
 // product directly.  K and V bytes are read once, with the streaming policy.
-// fp32 inputs take a vector-ALU path (d/4 lanes per row, all query heads of a
-// unit in one workgroup).
+// fp32 inputs take a vector-ALU path (d/4 lanes per row, up to eight of a unit's
+// query heads in one workgroup).
 #include <stdlib.h>
 
 #include <algorithm>
@@ -597,22 +597,9 @@ __global__ __launch_bounds__(512) void attn_split_bf16(AttnArgs a) {
   }
 }
 
-// Loads of K and of V per wave step (registers bound it).
-constexpr int f32_loads(int GP) { return 4; }
+// Loads of K and of V per wave step of the fp32 kernel (registers bound it).
+constexpr int kLoadsF32 = 4;
 
-// fp32 inputs on the vector ALU: one workgroup per (unit, split) for up to
-// GP = 1, 2, 4 or 8 of the unit's query heads together, so K and V are read
-// once (twice for 9 to 16 heads, whose state would not fit the registers)
-// and not once per query head.  A row is D / 4 lanes of
-// 16 bytes, so a wave load takes RPI whole rows; each step takes U loads of K
-// and of V, the next step's in flight while one is multiplied.  A lane keeps
-// 4 dims of every head's query and output; the dot products are summed over
-// a row's lanes by DPP moves.  What bounds it: HBM on many rows, the chain of
-// length, row id and row loads (about 7 us a launch) on few.  Against one
-// workgroup per query head, which read every row once per head with one load
-// in flight (at d 128, sets of 500 rows in 32 units of 4 heads: 27.3 -> 13.4
-// us; dense, 128 units of 4 heads over 4000 rows, 524 MB: 289 -> 99 us,
-// 5.3 TB/s).
 template <int U>
 struct F32Rows {
   float4 k[U], v[U];
@@ -711,10 +698,22 @@ __device__ __forceinline__ float over_row_groups(float v) {
   return v;
 }
 
+// fp32 inputs on the vector ALU: a workgroup per (unit, split) and GP = 1, 2, 4
+// or 8 of the unit's query heads together (launch_typed chooses), so a row of K
+// and V is read once for GP heads, ceil(heads / GP) times in all.  A row is D / 4
+// lanes of 16 bytes, so a wave load takes RPI whole rows; each step takes U loads
+// of K and of V, the next step's in flight while one is multiplied.  A lane keeps
+// 4 dims of every head's query and output; the dot products are summed over
+// a row's lanes by DPP moves.  What bounds it: HBM on many rows, the chain of
+// length, row id and row loads (about 7 us a launch) on few.  Against one
+// workgroup per query head, which read every row once per head with one load
+// in flight (at d 128, sets of 500 rows in 32 units of 4 heads: 27.3 -> 13.4
+// us; dense, 128 units of 4 heads over 4000 rows, 524 MB: 289 -> 99 us,
+// 5.3 TB/s).
 template <int D, int GP, bool DENSE>
 __global__ __launch_bounds__(64 * kMaxWaves) void attn_split_f32(AttnArgs a) {
   constexpr int LPR = D / 4, RPI = 64 / LPR;
-  constexpr int U = f32_loads(GP), ROWS = U * RPI;
+  constexpr int U = kLoadsF32, ROWS = U * RPI;
   // dynamic LDS: [nwaves][GP][D] wave outputs, then the staged row ids
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
   __shared__ float sm_m[kMaxWaves][16];
@@ -980,17 +979,11 @@ int wave_limit() {
 }
 
 template <int D, int GP, bool DENSE>
-hipError_t launch_f32(const AttnArgs& a, int units, int waves, hipStream_t stream) {
-  const size_t dyn = (size_t)waves * GP * D * sizeof(float) +
-                     (size_t)64 * waves * kRowsPerThread * sizeof(int32_t);
-  if (dyn > 65536) {
-    const hipError_t e = hipFuncSetAttribute((const void*)attn_split_f32<D, GP, DENSE>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
-    if (e != hipSuccess) return e;
-  }
+void launch_f32(const AttnArgs& a, int units, int waves, hipStream_t stream) {
+  constexpr int kWaveBytes = GP * D * (int)sizeof(float) + 64 * kRowsPerThread * (int)sizeof(int32_t);
+  static_assert(kMaxWaves * kWaveBytes <= 65536, "dynamic LDS that needs no attribute");
   hipLaunchKernelGGL((attn_split_f32<D, GP, DENSE>), dim3(a.nsplit, units * ((a.kv.hq / a.kv.hkv + GP - 1) / GP)),
-                     dim3(64 * waves), dyn, stream, a);
-  return hipSuccess;
+                     dim3(64 * waves), waves * kWaveBytes, stream, a);
 }
 
 template <int D, bool DENSE, bool PAGED>
@@ -1018,11 +1011,10 @@ hipError_t launch_typed(const AttnArgs& a, int dtype, int units, int waves, hipS
     const long long row_waves = (long long)units * a.nsplit * waves;   // of one workgroup a split
     int gp = G == 1 ? 1 : (G == 2 ? 2 : (G <= 4 ? 4 : 8));
     while (gp > 1 && row_waves * ((G + gp - 1) / gp) <= (gp > 2 ? 4 * device_cus() : device_cus() / 2)) gp >>= 1;
-    const hipError_t e = gp == 1   ? launch_f32<D, 1, DENSE>(a, units, waves, stream)
-                         : gp == 2 ? launch_f32<D, 2, DENSE>(a, units, waves, stream)
-                         : gp == 4 ? launch_f32<D, 4, DENSE>(a, units, waves, stream)
-                                   : launch_f32<D, 8, DENSE>(a, units, waves, stream);
-    if (e != hipSuccess) return e;
+    if (gp == 1) launch_f32<D, 1, DENSE>(a, units, waves, stream);
+    else if (gp == 2) launch_f32<D, 2, DENSE>(a, units, waves, stream);
+    else if (gp == 4) launch_f32<D, 4, DENSE>(a, units, waves, stream);
+    else launch_f32<D, 8, DENSE>(a, units, waves, stream);
   }
   if (a.nsplit > 1)
     hipLaunchKernelGGL((attn_merge<D, DENSE>), dim3(a.kv.batch * a.kv.hq), dim3(256), 0, stream,
