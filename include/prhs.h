@@ -164,8 +164,9 @@ int32_t prhs_max_topk(const prhs_params* params, int32_t max_seq_len);
 int32_t prhs_set_capacity(const prhs_params* params, int32_t max_seq_len);
 
 /* Device workspace in bytes that entry point `op` (PRHS_OP_*) needs for this
- * cache shape; set_cap is used by PRHS_OP_SPARSE_ATTN only.  0 bytes is a
- * valid answer (ws may then be NULL). */
+ * cache shape; set_cap is used by PRHS_OP_SPARSE_ATTN only.  For attention it
+ * also holds every call with a smaller batch, set_cap or max_seq_len and the
+ * rest the same.  0 bytes is a valid answer (ws may then be NULL). */
 prhs_status prhs_workspace_size(int32_t op, const prhs_kv* kv, const prhs_params* params,
                                 int32_t set_cap, size_t* bytes);
 

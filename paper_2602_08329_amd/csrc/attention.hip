@@ -1130,11 +1130,39 @@ hipError_t attn_static_scratch(void** ptr) {
   return hipSuccess;
 }
 
-size_t attn_workspace_bytes(int dtype, bool dense, int batch, int hq, int hkv, int d,
-                            int rows_cap) {
+size_t attn_call_bytes(int dtype, bool dense, int batch, int hq, int hkv, int d, int rows_cap) {
   int chunk, nsplit;
   attn_split_geometry(dtype, dense, batch, hq, hkv, d, rows_cap, &chunk, &nsplit);
   return attn_layout(batch, hq, d, nsplit).total;
+}
+
+// A program keeps one workspace for its largest batch and longest rows, and a
+// smaller call can want more of it: its units take more splits each (bf16 sets
+// of 2000 rows: 24 sequences of 8 units 192 splits in all, one sequence 256).
+// So the size is a bound over every smaller call, from what attn_split_geometry
+// may take: at most target_groups() workgroups or the fewest splits that staging
+// allows, a dense launch up to a split a unit more, or twice those splits.
+size_t attn_workspace_bytes(int dtype, bool dense, int batch, int hq, int hkv, int d,
+                            int rows_cap) {
+  const long long units = (long long)batch * hkv, rows = rows_cap > 0 ? rows_cap : 1;
+  const long long cmax = (dtype == 1 ? 64LL * wave_limit() : 256) * kRowsPerThread;
+  const long long least = (rows + cmax - 1) / cmax;
+  long long groups;   // splits of all units
+  if (!dense) {
+    const bool whole = rows <= (dtype == 1 ? kNoSplitRows : kNoSplitRowsF32) && rows <= cmax;
+    groups = whole ? units : std::max(target_groups(dtype, false, 0), units * least);
+  } else {
+    const long long set = dense_groups_override();
+    const long long halved = dtype == 1 && !set ? std::min(units, 128LL) : units;
+    groups = std::max({set ? set : kDenseGroups + (dtype == 1 ? units : 0), units * least,
+                       least > 1 ? 2 * halved * least : 0});
+  }
+  const int gran = dtype == 1 ? 32 : 16;
+  groups = std::min(groups, units * ((rows + gran - 1) / gran));
+  // the largest launch of any batch up to this one has at most that many splits
+  const long long per = units > 0 ? (groups + units - 1) / units : 0;
+  return std::max(attn_layout(batch, hq, d, (int)per).total,
+                  attn_call_bytes(dtype, dense, batch, hq, hkv, d, rows_cap));
 }
 
 hipError_t launch_attention(const AttnLaunch& s, bool dense, hipStream_t stream) {

@@ -358,8 +358,8 @@ static prhs_status attention_common(const prhs_kv* kv, const void* q, const int3
   double psaw_f = 0.0;
   if (psaw && (st = psaw_factor(psaw, &psaw_f)) != PRHS_OK) return st;
   const int rows_cap = dense ? kv->max_seq_len : set_cap;
-  const size_t wsz = prhs::attn_workspace_bytes(kv->dtype, dense, kv->batch, kv->num_q_heads,
-                                                kv->num_kv_heads, kv->head_dim, rows_cap);
+  const size_t wsz = prhs::attn_call_bytes(kv->dtype, dense, kv->batch, kv->num_q_heads,
+                                           kv->num_kv_heads, kv->head_dim, rows_cap);
   if (kv->batch > 0 && (!ws || ws_bytes < wsz))
     return fail(PRHS_E_WORKSPACE, "workspace of %zu bytes needed (got %zu)", wsz, ws_bytes);
   if (kv->batch == 0) return PRHS_OK;
@@ -402,8 +402,8 @@ prhs_status prhs_sparse_decode_attn_static(const prhs_kv* kv, const void* q,
   prhs_status st = check_kv_shape(kv);
   if (st != PRHS_OK) return st;
   if (set_cap < 0) return fail(PRHS_E_INVALID, "set_cap must be >= 0");
-  const size_t need = prhs::attn_workspace_bytes(kv->dtype, false, kv->batch, kv->num_q_heads,
-                                                 kv->num_kv_heads, kv->head_dim, set_cap);
+  const size_t need = prhs::attn_call_bytes(kv->dtype, false, kv->batch, kv->num_q_heads,
+                                            kv->num_kv_heads, kv->head_dim, set_cap);
   if (need > prhs::kStaticScratchBytes)
     return fail(PRHS_E_UNSUPPORTED,
                 "split-K partials of %zu bytes exceed the static scratch of %zu bytes", need,

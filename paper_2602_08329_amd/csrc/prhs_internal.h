@@ -275,6 +275,9 @@ struct AttnLaunch {
 // Split geometry shared by workspace sizing and launch.
 void attn_split_geometry(int dtype, bool dense, int batch, int hq, int hkv, int d, int rows_cap,
                          int* chunk, int* nsplit);
+// Workspace of one call, and one that also holds every call of fewer sequences
+// or rows.
+size_t attn_call_bytes(int dtype, bool dense, int batch, int hq, int hkv, int d, int rows_cap);
 size_t attn_workspace_bytes(int dtype, bool dense, int batch, int hq, int hkv, int d,
                             int rows_cap);
 hipError_t launch_attention(const AttnLaunch& a, bool dense, hipStream_t stream);

@@ -2,6 +2,8 @@
 the workspace a call asks for (its split-K partials): no device work."""
 
 import ctypes
+import math
+import random
 import re
 
 import pytest
@@ -77,3 +79,30 @@ def test_dense_bf16_splits(batch, hkv, d, rows, want):
 ])
 def test_f32_splits(batch, hq, hkv, d, rows, dense, want):
     assert splits("f32", batch, hq, hkv, d, rows, dense) == want
+
+
+def size(dtype, batch, hq, hkv, d, rows, dense):
+    c, n = kv(dtype, batch, hq, hkv, d, rows), ctypes.c_size_t(0)
+    op = B.PRHS_OP_DENSE_ATTN if dense else B.PRHS_OP_SPARSE_ATTN
+    assert B.lib().prhs_workspace_size(op, ctypes.byref(c), None, rows, ctypes.byref(n)) == B.PRHS_OK
+    return n.value
+
+
+def test_a_workspace_holds_every_smaller_call():
+    assert need("bf16", 1, 8, 8, 128, 2000, False) <= size("bf16", 24, 8, 8, 128, 2000, False)
+    rng = random.Random(11)
+
+    def log(a, b):
+        return int(math.exp(rng.uniform(math.log(a), math.log(b))))
+    for _ in range(20000):
+        dtype, dense = rng.choice(["bf16", "f32"]), rng.random() < 0.5
+        hkv, g, d = rng.choice([1, 2, 3, 4, 8, 16, 32]), rng.choice([1, 2, 3, 4, 8, 16]), rng.choice([64, 128])
+        most, rows = log(1, 400), log(1, 200000)
+        batch, r = rng.choice([most, rng.randint(1, most)]), rng.choice([rows, rng.randint(1, rows), log(1, rows)])
+        if most * hkv * rows >= 2**31:
+            continue
+        held = size(dtype, most, hkv * g, hkv, d, rows, dense)
+        assert need(dtype, batch, hkv * g, hkv, d, r, dense) <= held, (dtype, dense, hkv, g, d, most, rows, batch, r)
+        # and is no multiple of what the largest call takes
+        assert held <= max(2.1 * need(dtype, most, hkv * g, hkv, d, rows, dense),
+                           (1024 + 2 * most * hkv) * g * (d + 2) * 4 + 256)
