@@ -389,7 +389,7 @@ prhs_status prhs_gate(int32_t batch, int32_t num_q_heads, int32_t num_kv_heads, 
  * prhs_select_gated (set_idx / shared_idx: the current slot's pool rows of
  * kind 0 and 1).  q and seq_lens come from kv and the query argument.  When
  * the refresh runs as one fused launch (bf16 cache, middle range within one
- * CU's LDS, rows filling more than half the CUs or very short) the gate is
+ * CU's LDS, rows filling enough of the CUs or very short) the gate is
  * taken inside that launch, one wave per row before it scores; otherwise
  * the gate kernel runs first.  The decided units' outputs of this step
  * (choice, row_anchor, row_other, tail) are written before any of them is

@@ -6,8 +6,8 @@
 // gate sends to retrieval.
 //
 // Three paths, all on the caller's stream (select_path picks one):
-//   select_fused   middle range within LDS, bf16, rows filling more than half
-//                  the CUs (or very short): one workgroup per row scores into
+//   select_fused   middle range within LDS, bf16, rows filling enough of the
+//                  CUs (or very short): one workgroup per row scores into
 //                  LDS, takes exact thresholds for k and m over the 32-bit
 //                  keys and compacts in position order (which settles ties)
 //                  -- one launch;
@@ -1866,20 +1866,30 @@ namespace {
 
 enum class SelPath { kFused, kKeyed, kRadix };
 
-// The refresh's launch sequence.  Middle ranges that fit LDS: one fused
-// launch when the rows (one workgroup each) fill more than half the CUs, or
-// are so short (kFusedShortBytes of K) that a launch of their own costs more
-// than reading them by one workgroup each, and the cache is bf16; else scoring
-// spread over many workgroups per row followed by one selection workgroup per
-// row (keyed).  Longer middle ranges: the radix path (score, filter, finish).
+// The refresh's launch sequence.  Middle ranges that fit LDS and a bf16 cache:
+// one fused launch, a workgroup a row, when the rows fill more than half the CUs
+// (for long rows, kLongKeyed keys or more, five eighths) or are so short
+// (kFusedShortBytes of K) that a launch of their own costs more than reading them
+// by one workgroup each; else scoring spread over many workgroups per row
+// followed by one selection workgroup per row (keyed).  Longer middle ranges: the
+// radix path (score, filter, finish).
 // Fused / keyed, us: 4 rows of 400 keys at d 64 11.2 / 12.7, of 1000 13.7 /
 // 13.4; 128 rows of 400 at d 128 15.7 / 16.3, of 1000 20.7 / 19.9; 152 rows of
-// 1000 20.8 / 22.1, of 4000 43.4 / 41.8; 256 of 4000 56.4 / 58.5; paged, 16
-// tokens a page, 384 rows of 4k to 8k 120 / 143, 512 of 8k to 16k 283 / 316,
-// 512 of 500 to 1000 30.9 / 37.6 (350 and 46 before the paged form).
+// 1000 20.8 / 22.1; 160 of 1900 24.7 / 27.6; of long rows 129 of 4070 at d 64
+// 26.7 / 26.1, of 11139 54.5 / 49.6, 136 of 21374 157 / 143, paged 132 ragged ones
+// of 7018 56.0 / 48.7, 136 of 16080 at d 64 88.0 / 74.1, 160 of 12737 91.4 / 86.8,
+// but 176 of 10901 92.7 / 103, 192 of 7550 at d 64 44.5 / 47.8, 256 of 9676 95.2 /
+// 95.6; paged, 16 tokens a page, 384 rows of 4k to 8k 120 / 143, 512 of 8k to 16k
+// 283 / 316, 512 of 500 to 1000 30.9 / 37.6 (350 and 46 before the paged form).
+// Under the similarity gate the rows that share leave their CUs idle, so long rows
+// go fused from seven eighths of the CUs only (every row retrieving, then half of
+// them: 144 of 12000 96.6 / 94.9 and 89.1 / 60.5, paged 160 of 16000 129 / 138 and
+// 117 / 83.6, 192 of 16000 144 / 162 and 124 / 94.8, but 256 of 8000 99.0 / 110 and
+// 69.5 / 68.5).
 // PRHS_SELECT_PATH=fused|keyed|split forces a path where it applies.
 constexpr long long kFusedShortBytes = 100 * 1024;
-SelPath select_path(int dtype, int d, int rows, int mcap) {
+constexpr int kLongKeyed = 4000;
+SelPath select_path(int dtype, int d, int rows, int mcap, bool gated) {
   static const int force = [] {
     const char* e = getenv("PRHS_SELECT_PATH");
     if (!e) return 0;
@@ -1895,7 +1905,8 @@ SelPath select_path(int dtype, int d, int rows, int mcap) {
   if (force == 3) return SelPath::kRadix;
   if (!fits) return SelPath::kRadix;
   const int cus = device_cus();
-  if (fused_ok && (cus <= 0 || 2 * rows > cus || (long long)mcap * d * 2 <= kFusedShortBytes))
+  const int eighths = mcap < kLongKeyed ? 4 : (gated ? 7 : 5);   // of the CUs that fused rows exceed
+  if (fused_ok && (cus <= 0 || 8LL * rows > (long long)eighths * cus || (long long)mcap * d * 2 <= kFusedShortBytes))
     return SelPath::kFused;
   return SelPath::kKeyed;
 }
@@ -1979,7 +1990,7 @@ hipError_t launch_select(const SelectLaunch& s, hipStream_t stream) {
   const int ps = s.kv.page_size;
   a.page_shift = ps > 0 && (ps & (ps - 1)) == 0 ? __builtin_ctz(ps) : -1;
 
-  const SelPath path = select_path(s.dtype, s.kv.d, rows, a.mcap);
+  const SelPath path = select_path(s.dtype, s.kv.d, rows, a.mcap, s.gate != nullptr);
   if (s.gate) {
     if (path == SelPath::kFused) {
       a.gate_fused = 1;   // the gate runs inside the refresh launch

@@ -16,6 +16,7 @@ import torch
 import oracle as O
 from paper_2602_08329_amd import binding as B
 from paper_2602_08329_amd import synth
+from tests.test_prefill_plan import FORMS, WINDOW
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -188,12 +189,12 @@ def test_prefill_rejects_fp32():
 
 
 @pytest.mark.parametrize("batch,hq,T,d,paged", [
-    (1, 2, 127, 128, False),    # four key sides: the edges of 64-query blocks and 128-key tiles
-    (1, 2, 129, 64, True),
+    (1, 2, 127, 128, False),    # one block of 128 queries, 16 a wave, two 64-key tiles
+    (1, 2, 129, 64, True),      # 16-query waves, two blocks of 80
     (3, 24, 257, 128, True),    # two key sides: 128-query blocks (on 256 CUs)
     (3, 24, 384, 64, False),
     (3, 60, 255, 128, False),   # one key side: 256-query blocks, units not a multiple of the XCDs
-    (5, 24, 321, 128, True),    # units a multiple of the XCDs, not of a whole group of them
+    (5, 24, 321, 128, True),    # units a multiple of the XCDs
     (2, 64, 537, 128, False),   # a first block smaller than the others
     (1, 60, 97, 64, True),      # blocks smaller than their waves allow
     (2, 64, 173, 128, True),    # 16-query waves, two blocks
@@ -209,3 +210,21 @@ def test_prefill_key_sides_and_block_order(batch, hq, T, d, paged):
     run_prefill(batch, hq, min(hq, 4), d, lens, T, psaw=(2, 0.6, 1.0), layer=3, n_layers=4, sink=5,
                 seed=41 + T, rows=[r for r in rows if 0 <= r < T], heads=[0, hq // 2, hq - 1],
                 paged=paged)
+
+
+@pytest.mark.parametrize("w,ns,d,paged,batch,hq,T", FORMS)
+def test_prefill_every_form(w, ns, d, paged, batch, hq, T):
+    # rows at the edges of 32- and 64-query waves, of blocks and of 128-key tiles
+    lens = tuple(max(1, T - 61 * i) for i in range(batch))
+    rows = sorted({r for e in range(0, T + 1, 64) for r in (e - 1, e)} | {16, 31, 32, 33, T // 2, T - 62, T - 1})
+    rows = [r for r in rows if 0 <= r < T] if T < 900 else [0, 31, 255, 256, 511, 512, 767, 768, 939, T - 1]
+    run_prefill(batch, hq, min(hq, 4), d, lens, T, seed=51 + T, rows=rows, heads=[0, hq // 2, hq - 1],
+                paged=paged, **WINDOW)
+
+
+def test_prefill_order_in_several_groups():
+    # 40 units an XCD in groups of 20, the last block of each prompt short; and 5 an
+    # XCD, fewer blocks than its CUs
+    for batch, hq, T in ((4, 80, 1790), (1, 40, 600)):
+        run_prefill(batch, hq, 8, 64, (T,) * batch, T, seed=61 + T, rows=[0, 255, 256, T - 255, T - 1],
+                    heads=[0, 1, hq // 2, hq - 1])

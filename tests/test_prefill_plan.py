@@ -13,6 +13,22 @@ from paper_2602_08329_amd import build
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
+# launches of every form of the kernel on 256 CUs: waves of w queries, ns key
+# sides, d, paged, and batch, query heads and T under the window of WINDOW
+FORMS = [
+    (16, 1, 128, False, 1, 64, 113), (16, 1, 128, True, 2, 64, 173),
+    (32, 1, 128, False, 3, 60, 255), (32, 1, 128, True, 5, 24, 321),
+    (32, 2, 128, False, 1, 60, 257), (32, 2, 128, True, 3, 24, 257),
+    (32, 4, 128, False, 2, 4, 300), (32, 4, 128, True, 2, 8, 777),
+    (16, 1, 64, False, 2, 64, 265), (16, 1, 64, True, 1, 60, 97),
+    (32, 1, 64, False, 4, 64, 300), (32, 1, 64, True, 3, 48, 300),
+    (32, 2, 64, False, 3, 24, 384), (32, 2, 64, True, 1, 48, 330),
+    (32, 4, 64, False, 1, 4, 500), (32, 4, 64, True, 1, 48, 300),
+    # blocks for every CU eight times over: 256 queries whatever else
+    (32, 1, 64, True, 8, 64, 1000),
+]
+WINDOW = dict(psaw=(2, 0.6, 1.0), layer=3, n_layers=4, sink=5)
+
 
 @pytest.fixture(scope="module")
 def ask(tmp_path_factory):
@@ -102,3 +118,14 @@ def test_left_over_queries_of_a_long_prompt_come_last(ask):
     # 64 blocks for 32 CUs an XCD; and queries, not key sides, where two a CU follow
     assert [r[:4] for r in ask(["plan " + shape(12197, 8), "plan " + shape(11000, 8),
                                 "plan " + shape(10611, 8, 128, 0, 1, 0.2)])] == [["16", "1", "192", "192"]] * 3
+
+
+def test_forms_are_those_the_launches_take(ask):
+    l_s, phi, alpha = WINDOW["psaw"]
+    factor = 1 - phi ** (alpha * (WINDOW["layer"] + 1 - l_s) / (WINDOW["n_layers"] - l_s))
+    got = ask(["plan " + shape(T, batch * hq, d, int(paged), 1, factor, WINDOW["sink"])
+               for _, _, d, paged, batch, hq, T in FORMS])
+    for form, r in zip(FORMS, got):
+        assert tuple(map(int, r[:2])) == form[:2], (form, r)
+    assert {f[:4] for f in FORMS} == {(w, ns, d, paged) for w, ns in ((16, 1), (32, 1), (32, 2), (32, 4))
+                                      for d in (64, 128) for paged in (False, True)}
