@@ -67,13 +67,13 @@ constexpr int kNoSplitRowsF32 = 256;
 constexpr int kNoSplitManyF32 = 450, kManyF32 = 40;
 constexpr int kNoSplitHeadRowsF32 = 2048;
 // fp32 splits: at least kMinRowsF32 rows (half of that where the splits of all
-// heads are fewer than kFewHeadsF32: one unit of 8 heads over 377 rows 8.7 -> 7.6
-// us), and no more than kMergeSplitsF32 of them per unit once the launch has 256
-// workgroups, since the merge reads every split's output of every head (dense, 8
-// units of 4 heads at d 128: 2000 rows in 125 splits 18.3 us, in 32 13.6; 8000
-// rows in 125 26.5, in 32 19.8).
+// heads are fewer than kFewHeadsF32: one unit of 8 heads over 377 rows 8.7 -> 7.6,
+// 4 of 16 over 178 9.3 -> 8.5 us), and no more than kMergeSplitsF32 of them per
+// unit once the launch has 256 workgroups, since the merge reads every split's
+// output of every head (dense, 8 units of 4 heads at d 128: 2000 rows in 125
+// splits 18.3 us, in 32 13.6; 8000 rows in 125 26.5, in 32 19.8).
 constexpr int kMinRowsF32 = 64;
-constexpr long long kFewHeadsF32 = 192;
+constexpr long long kFewHeadsF32 = 256;
 constexpr long long kMergeSplitsF32 = 32;
 
 struct AttnArgs {
