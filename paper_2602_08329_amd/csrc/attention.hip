@@ -56,15 +56,19 @@ constexpr int kMaxWaves = 8;        // waves of an attention workgroup
 // Sparse sets of at most this many rows per unit are not split: a launch of
 // one workgroup per unit beats a split launch plus its merge launch (fp32
 // rows are twice as long: 32 units of 500 rows 20.7 us unsplit, 13.4 split; 4
-// units of 150 rows 5.6 and 7.9).  Dense fp32 streams the same, and up to
+// units of 150 rows 5.6 and 7.9).  Dense fp32 streams the same; up to
 // kNoSplitManyF32 rows where kManyF32 units keep the chip busy (64 units of 16
 // heads over 146 rows at d 128 19.4 us in three splits, 11.4 unsplit, 48 of 338
-// 25.6 and 17.8), fewer where few units have many heads (kNoSplitHeadRowsF32 rows
-// times heads: 12 units of 16 heads over 219 rows 10.0 us in four splits, 11.6
-// unsplit; 32 of 8 over 203 9.0 and 7.4).
+// 25.6 and 17.8); up to kNoSplitMostF32 where kMostF32 do (160 of 16 over 490 at
+// d 64 39.6 and 27.5, 200 of 4 over 700 46 and 29.9, 160 of 1 over 1120 23 and
+// 18; but 160 of 8 over 1989 89 and 102, 96 of 4 over 879 16.6 and 18.3); and
+// fewer where few units have many heads (kNoSplitHeadRowsF32 rows times heads: 12
+// units of 16 heads over 219 rows 10.0 us in four splits, 11.6 unsplit; 32 of 8
+// over 203 9.0 and 7.4).
 constexpr int kNoSplitRows = 512;
 constexpr int kNoSplitRowsF32 = 256;
 constexpr int kNoSplitManyF32 = 450, kManyF32 = 40;
+constexpr int kNoSplitMostF32 = 1200, kMostF32 = 128;
 constexpr int kNoSplitHeadRowsF32 = 2048;
 // fp32 splits: at least kMinRowsF32 rows (half of that where the splits of all
 // heads are fewer than kFewHeadsF32: one unit of 8 heads over 377 rows 8.7 -> 7.6,
@@ -1003,14 +1007,17 @@ hipError_t launch_typed(const AttnArgs& a, int dtype, int units, int waves, hipS
     // heads per workgroup: all (up to 8), or fewer while the launch has at most
     // a wave for each of the four SIMDs of a CU, where the heads' serial work
     // costs more than reading the rows again from the caches, and a workgroup a
-    // head where half the CUs get a wave at most (8 units of 8 heads over 60 rows
-    // at d 64: 8 heads 8.0 us, 4 6.3, 2 5.8, 1 6.1; 48 of 16 over 338 rows at d
-    // 128: 8 heads a workgroup 21, 4 17.8, 2 24; 112 of 16 over 82 rows 15.3,
-    // 20.0 and -; one of 8 over 377 rows in 12 splits 2 heads 8.8, 1 7.5)
+    // head where half the CUs get a wave at most (but unsplit for up to four; 8 units of 8
+    // heads over 60 rows at d 64: 8 heads 8.0 us, 4 6.3, 2 5.8, 1 6.1; 48 of 16
+    // over 338 rows at d 128: 8 heads a workgroup 21, 4 17.8, 2 24; 112 of 16 over
+    // 82 rows 15.3, 20.0 and -; one of 8 over 377 rows in 12 splits 2 heads 8.8, 1
+    // 7.5; unsplit 12 of 4 over 133 5.9 and 5.3, but 2 of 8 over 198 8.5 and 9.3)
     const int G = a.kv.hq / a.kv.hkv;
     const long long row_waves = (long long)units * a.nsplit * waves;   // of one workgroup a split
     int gp = G == 1 ? 1 : (G == 2 ? 2 : (G <= 4 ? 4 : 8));
-    while (gp > 1 && row_waves * ((G + gp - 1) / gp) <= (gp > 2 ? 4 * device_cus() : device_cus() / 2)) gp >>= 1;
+    // waves up to which gp is halved, from 2 and from more
+    const int halve[2] = {a.nsplit > 1 || G <= 4 ? device_cus() / 2 : 0, 4 * device_cus()};
+    while (gp > 1 && row_waves * ((G + gp - 1) / gp) <= halve[gp > 2]) gp >>= 1;
     if (gp == 1) launch_f32<D, 1, DENSE>(a, units, waves, stream);
     else if (gp == 2) launch_f32<D, 2, DENSE>(a, units, waves, stream);
     else if (gp == 4) launch_f32<D, 4, DENSE>(a, units, waves, stream);
@@ -1094,7 +1101,9 @@ void attn_split_geometry(int dtype, bool dense, int batch, int hq, int hkv, int 
   if (c < cmin) c = cmin;
   long long whole = dtype == 1 ? (dense ? 0 : kNoSplitRows) : kNoSplitRowsF32;
   if (dense && dtype != 1)
-    whole = units >= kManyF32 ? kNoSplitManyF32 : std::min(whole, (long long)kNoSplitHeadRowsF32 * hkv / hq);
+    whole = units >= kMostF32   ? kNoSplitMostF32
+            : units >= kManyF32 ? kNoSplitManyF32
+                                : std::min(whole, (long long)kNoSplitHeadRowsF32 * hkv / hq);
   if (rows <= whole && rows <= cmax) c = rows;
   if (c > cmax) c = cmax;
   if (c < gran) c = gran;

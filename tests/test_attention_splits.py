@@ -43,7 +43,7 @@ def f32_heads(batch, hq, hkv, d, rows, dense):
     chunk = -(-(-(-rows // ns)) // 16) * 16
     waves = min(8, -(-chunk // (16 if units * ns < 2 * CUS else 32)))
     gp = 1 if g == 1 else 2 if g == 2 else 4 if g <= 4 else 8
-    while gp > 1 and units * ns * waves * -(-g // gp) <= (4 * CUS if gp > 2 else CUS // 2):
+    while gp > 1 and units * ns * waves * -(-g // gp) <= (4 * CUS if gp > 2 else CUS // 2 if ns > 1 or g <= 4 else 0):
         gp //= 2
     return gp
 
@@ -70,7 +70,8 @@ def test_dense_bf16_splits(batch, hkv, d, rows, want):
     # short rows unsplit, sets and streams
     (1, 4, 4, 64, 256, False, 1), (64, 1, 1, 64, 257, False, 4), (1, 4, 4, 64, 256, True, 1),
     (1, 16, 1, 64, 128, True, 1), (6, 32, 2, 64, 129, True, 3),
-    (40, 16, 1, 128, 450, True, 1), (40, 16, 1, 128, 451, True, 8), (39, 2, 1, 128, 257, True, 5),
+    (40, 16, 1, 128, 450, True, 1), (40, 16, 1, 128, 451, True, 8), (127, 8, 1, 64, 1000, True, 8),
+    (128, 8, 1, 64, 1200, True, 1), (128, 8, 1, 64, 1201, True, 8), (160, 1, 1, 128, 1120, True, 1), (39, 2, 1, 128, 257, True, 5),
     # few heads: splits of 32 rows up to 1024 of them, else of 64
     (1, 8, 1, 128, 377, True, 12), (1, 2, 1, 64, 1024, False, 32), (1, 2, 1, 64, 1025, False, 17),
     (12, 16, 1, 128, 1000, True, 16),

@@ -68,6 +68,7 @@ F32_FORMS = [
     (8, 8, 16, 80, 16, 128, False, 270),
     (8, 8, 4, 128, 8, 64, False, 1100),
     (8, 8, 16, 144, 16, 64, True, 300),
+    (8, 8, 17, 64, 8, 64, True, 1200),   # the stream unsplit
 ]
 
 
