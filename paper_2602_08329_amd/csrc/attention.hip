@@ -972,15 +972,15 @@ long long many_unit_splits(long long units, long long rows, int d, long long cma
   return !few_over && over > 0 && over <= kDenseSlots / 4 && k > least ? k - 1 : k;
 }
 
-// Waves per bf16 workgroup: PRHS_ATTN_WAVES overrides the default of 4.
-int wave_limit() {
-  static int v = [] {
-    const char* e = getenv("PRHS_ATTN_WAVES");
-    const int x = e ? atoi(e) : 0;
-    return x >= 1 && x <= 8 ? x : 4;
+// Waves per bf16 workgroup: 4, or what PRHS_ATTN_WAVES sets (0: not set).
+int wave_override() {
+  static const int v = [] {
+    const int x = env_int("PRHS_ATTN_WAVES", 0);
+    return x <= kMaxWaves ? x : 0;
   }();
   return v;
 }
+int wave_limit() { return wave_override() ? wave_override() : 4; }
 
 template <int D, int GP, bool DENSE>
 void launch_f32(const AttnArgs& a, int units, int waves, hipStream_t stream) {
@@ -1056,7 +1056,8 @@ int waves_for(int dtype, bool dense, long long groups, int chunk) {
   // 8.0 us, 16 of 500 11.5 -> 11.0, 72 of 280 at d 64 7.5 -> 7.1; 64 of 200
   // 8.6 -> 9.0, 384 of 640 30.0 -> 32.9)
   int w = chunk / 32;
-  const int lim = wave_limit() * (!dense && groups <= device_cus() && chunk >= 256 ? 2 : 1);
+  const bool twice = !dense && groups <= device_cus() && chunk >= 256 && !wave_override();
+  const int lim = wave_limit() * (twice ? 2 : 1);
   return w < 1 ? 1 : std::min({w, lim, kMaxWaves});
 }
 
