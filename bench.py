@@ -306,24 +306,27 @@ def cpu_baseline(run, budget_s):
 ROOT = os.path.dirname(os.path.abspath(__file__))
 
 
-def committed_traffic(profile, source):
+def committed_traffic(profile, *sources):
     """HBM bytes per launch of a kernel measured with rocprofv3 counters
     (FETCH_SIZE and WRITE_SIZE, scaled by a plain-copy calibration) and
-    recorded in profiles/<profile>; None when there is no record or the
-    kernel's source file (csrc/<source>) changed since it was taken."""
+    recorded in profiles/<profile>; None when there is no record or one of
+    the kernel's source files (csrc/<source>) changed since it was taken."""
     import hashlib
     path = os.path.join(ROOT, "profiles", profile)
-    src = os.path.join(ROOT, "paper_2602_08329_amd", "csrc", source)
-    if not os.path.exists(path) or not os.path.exists(src):
+    csrc = os.path.join(ROOT, "paper_2602_08329_amd", "csrc")
+    if not os.path.exists(path):
         return None
-    digest = hashlib.sha256(open(src, "rb").read()).hexdigest()
     fields = {}
     for line in open(path):
         if ":" in line and line.startswith("- "):
             k, v = line[2:].split(":", 1)
             fields[k.strip()] = v.strip().strip("`")
-    if fields.get(f"{source} sha256") != digest:
-        return None
+    for source in sources:
+        src = os.path.join(csrc, source)
+        if not os.path.exists(src):
+            return None
+        if fields.get(f"{source} sha256") != hashlib.sha256(open(src, "rb").read()).hexdigest():
+            return None
     try:
         return int(fields["traffic bytes per launch"])
     except (KeyError, ValueError):
@@ -482,7 +485,8 @@ def prefill_main(args):
         "roofline": {"kernel": "attn_prefill_bf16", "bound": "mfma", "achieved": round(tflops, 1),
                      "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(tflops / MFMA_BF16_PEAK_TFLOPS, 4),
-                     "traffic": committed_traffic(f"attn_prefill_bf16_{workload}.md", "prefill.hip"),
+                     "traffic": committed_traffic(f"attn_prefill_bf16_{workload}.md", "prefill.hip",
+                                                 "prefill_plan.h"),
                      "causal_achieved": round(tflops_causal, 1),
                      "note": "useful flops (4 d per visible query-key pair and head) over the "
                              "timed prefill; the kernel issues more (16-column tiles, the "

@@ -1054,7 +1054,10 @@ int waves_for(int dtype, bool dense, long long groups, int chunk) {
   // twice the waves for at least two tiles each while every workgroup has a CU
   // to itself: more of the set's rows load at once (8 units of 300 rows 8.8 ->
   // 8.0 us, 16 of 500 11.5 -> 11.0, 72 of 280 at d 64 7.5 -> 7.1; 64 of 200
-  // 8.6 -> 9.0, 384 of 640 30.0 -> 32.9)
+  // 8.6 -> 9.0, 384 of 640 30.0 -> 32.9).  Such a workgroup leaves no room on its
+  // CU for another launch's; the gate's two branches on two streams lose nothing
+  // by it (blocks of 4 steps, four waves -> eight, us: 16 x 8 units 398 -> 384, 8 x
+  // 32 467 -> 464, 4 x 8 433 -> 431, 2 x 32 521 -> 522)
   int w = chunk / 32;
   const bool twice = !dense && groups <= device_cus() && chunk >= 256 && !wave_override();
   const int lim = wave_limit() * (twice ? 2 : 1);

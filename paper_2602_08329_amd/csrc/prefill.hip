@@ -31,12 +31,12 @@
 // 32 queries per wave halve the LDS reads per product of 16 (16 KB per 32
 // keys): one prompt of 32 heads x 16384 at d 128 went from 6.4 to 5.8
 // million cycles, while the clock under this load fell from 2.10 to 2.05 GHz:
-// 2848 -> 2784 us, 1185 TFLOP/s issued with the probabilities' low part (a
-// large plain bf16 product reaches 1414 on this card).  32 heads x 4096 went
-// from 235 to 190 us, two paged prompts of 12k under PSAW (8 key heads) from
-// 2657 to 2339, 64 heads x 7777 at d 64 from 1018 to 731, 16 heads x 1122
-// from 48 to 26.  Short prompts on many units and single rounds of blocks
-// keep the 16.  Two groups of waves held half a step apart by barriers (one
+// 2971 -> 2900 us in turn on one card, 1137 TFLOP/s issued with the
+// probabilities' low part (a large plain bf16 product of normal data reached
+// 1394 there, of zeros 1793).  32 heads x 4096 went from 246 to 204 us, two
+// paged prompts of 12k under PSAW (8 key heads) from 2712 to 2495, 64 heads x
+// 7777 at d 64 from 1026 to 749, 16 heads x 1122 from 48.5 to 25.6.  Short
+// prompts on many units and single rounds of blocks keep the 16.  Two groups of waves held half a step apart by barriers (one
 // group's products beside the other's softmax) took the same cycles; dot
 // products for the remainders p - hi were slower, and raised issue priority
 // for the products changed nothing.
