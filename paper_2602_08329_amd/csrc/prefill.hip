@@ -36,10 +36,11 @@
 // 1394 there, of zeros 1793).  32 heads x 4096 went from 246 to 204 us, two
 // paged prompts of 12k under PSAW (8 key heads) from 2712 to 2495, 64 heads x
 // 7777 at d 64 from 1026 to 749, 16 heads x 1122 from 48.5 to 25.6.  Short
-// prompts on many units and single rounds of blocks keep the 16.  Two groups of waves held half a step apart by barriers (one
-// group's products beside the other's softmax) took the same cycles; dot
-// products for the remainders p - hi were slower, and raised issue priority
-// for the products changed nothing.
+// prompts on many units and single rounds of blocks keep the 16.  Two groups
+// of waves held half a step apart by barriers (one group's products beside
+// the other's softmax) took the same cycles; dot products for the remainders
+// p - hi were slower, and raised issue priority for the products changed
+// nothing.
 #include <type_traits>
 
 #include "prefill_plan.h"
